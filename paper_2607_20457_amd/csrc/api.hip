@@ -312,8 +312,14 @@ int pulsar_phase2_partial(const void* q, const void* K, const void* V, int n_sha
   if (S > 0 && (K == nullptr || V == nullptr)) return PULSAR_EINVAL;
   if (!aligned16(q) || (S > 0 && (!aligned16(K) || !aligned16(V))) || !aligned16(o_parts))
     return PULSAR_EINVAL;
-  const int ns = phase2_splits(n_shards, Tq, S, Hq, Hkv, d);
-  const size_t need = pulsar_phase2_workspace_bytes(n_shards, Tq, S, Hq, Hkv, d);
+  int ns = phase2_splits(n_shards, Tq, S, Hq, Hkv, d);
+  size_t need = pulsar_phase2_workspace_bytes(n_shards, Tq, S, Hq, Hkv, d);
+  // a few rows over short shards also run without a workspace, one wave per
+  // shard and KV head
+  if (workspace == nullptr && S <= 256 && decode_applies(Tq, Hq, Hkv, d)) {
+    ns = 1;
+    need = 0;
+  }
   if (need > 0 && (workspace == nullptr || workspace_bytes < need || !aligned16(workspace)))
     return PULSAR_EWORKSPACE;
 
@@ -394,24 +400,31 @@ struct QueryPlan {
   int np_shard, np_gen;  // key ranges per shard / of the generation shard's rows
   int parts;
 };
-QueryPlan query_plan(int n_shards, int Tq, int64_t S, int64_t G, int Hq, int Hkv, int d) {
+QueryPlan query_plan(int n_shards, int Tq, int64_t S, int64_t G, int Hq, int Hkv, int d,
+                     int min_keys) {
   QueryPlan p{};
   p.decode = decode_applies(Tq, Hq, Hkv, d);
   p.gen_decode = p.decode || ((d == 64 || d == 128) && Hq / Hkv <= 32 && G + Tq <= kGenDecodeRows &&
                                (int64_t)Tq * (Hq / Hkv) <= kGenDecodeQueryRows);
   if (p.decode) {
-    p.np_shard = decode_parts(n_shards, S, Hkv);
+    p.np_shard = decode_parts(n_shards, S, Hkv, min_keys);
   } else {
     p.np_shard = n_shards > 0 ? phase2_splits(n_shards, Tq, S, Hq, Hkv, d) : 0;
   }
   if (p.gen_decode) {
-    p.np_gen = decode_parts(1, G + Tq, Hkv);
+    p.np_gen = decode_parts(1, G + Tq, Hkv, min_keys);
     p.parts = n_shards * p.np_shard + p.np_gen;
   } else {
     p.np_gen = G > 0 ? phase2_splits(1, Tq, G, Hq, Hkv, d) : 0;
     p.parts = n_shards * p.np_shard + p.np_gen + 1;
   }
   return p;
+}
+
+// Workspace of a plan's partials: o, then lse, each 16-byte aligned.
+size_t parts_bytes(const QueryPlan& plan, int Tq, int Hq, int d) {
+  const size_t parts = (size_t)plan.parts;
+  return align16(parts * Tq * Hq * d * 4) + align16(parts * Hq * Tq * 4);
 }
 
 // Unmasked attention of the Tq queries over nz key sets of S rows each, every
@@ -451,9 +464,7 @@ size_t pulsar_phase2_query_workspace_bytes(int n_shards, int Tq, int64_t S, int6
                                            int Hkv, int d) {
   if (n_shards < 0 || Tq < 0 || S < 0 || G < 0 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0 || d < 1)
     return 0;
-  const QueryPlan plan = query_plan(n_shards, Tq, S, G, Hq, Hkv, d);
-  const size_t parts = (size_t)plan.parts;
-  return align16(parts * Tq * Hq * d * 4) + align16(parts * Hq * Tq * 4);
+  return parts_bytes(query_plan(n_shards, Tq, S, G, Hq, Hkv, d, kDecodeMinKeys), Tq, Hq, d);
 }
 
 }  // extern "C"
@@ -504,20 +515,13 @@ int scratch_of_current_device(void** out) {
 }
 }  // namespace
 
-extern "C" {
-
-int pulsar_phase2_query(const void* q, const void* Kg, const void* Vg, int64_t G, const void* K,
-                        const void* V, int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d,
-                        float softmax_scale, float* o, float* lse, void* workspace,
-                        size_t workspace_bytes, void* stream) {
-  const int chk = phase2_query_check(q, Kg, Vg, G, K, V, n_shards, Tq, S, Hq, Hkv, d,
-                                     softmax_scale, o);
-  if (chk != PULSAR_OK || Tq == 0) return chk;
-  const size_t need = pulsar_phase2_query_workspace_bytes(n_shards, Tq, S, G, Hq, Hkv, d);
-  if (workspace == nullptr || workspace_bytes < need || !aligned16(workspace))
-    return PULSAR_EWORKSPACE;
-
-  const QueryPlan plan = query_plan(n_shards, Tq, S, G, Hq, Hkv, d);
+namespace {
+// A checked Phase-2 query step (Tq > 0) by `plan`, through a workspace of
+// at least parts_bytes.
+int phase2_query_run(const QueryPlan& plan, const void* q, const void* Kg, const void* Vg,
+                     int64_t G, const void* K, const void* V, int n_shards, int Tq, int64_t S,
+                     int Hq, int Hkv, int d, float softmax_scale, float* o, float* lse,
+                     void* workspace, void* stream) {
   const int parts = plan.parts;
   const int64_t ostride = (int64_t)Tq * Hq * d, lstride = (int64_t)Hq * Tq;
   float* po = static_cast<float*>(workspace);
@@ -589,6 +593,24 @@ int pulsar_phase2_query(const void* q, const void* Kg, const void* Vg, int64_t G
   return launch_lse_merge(po, pl, parts, 1, Tq, Hq, d, ostride, lstride, o, lse,
                           (hipStream_t)stream);
 }
+}  // namespace
+
+extern "C" {
+
+int pulsar_phase2_query(const void* q, const void* Kg, const void* Vg, int64_t G, const void* K,
+                        const void* V, int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d,
+                        float softmax_scale, float* o, float* lse, void* workspace,
+                        size_t workspace_bytes, void* stream) {
+  const int chk = phase2_query_check(q, Kg, Vg, G, K, V, n_shards, Tq, S, Hq, Hkv, d,
+                                     softmax_scale, o);
+  if (chk != PULSAR_OK || Tq == 0) return chk;
+  const QueryPlan plan = query_plan(n_shards, Tq, S, G, Hq, Hkv, d, kDecodeMinKeys);
+  if (workspace == nullptr || workspace_bytes < parts_bytes(plan, Tq, Hq, d) ||
+      !aligned16(workspace))
+    return PULSAR_EWORKSPACE;
+  return phase2_query_run(plan, q, Kg, Vg, G, K, V, n_shards, Tq, S, Hq, Hkv, d, softmax_scale, o,
+                          lse, workspace, stream);
+}
 
 int pulsar_phase2_query_noalloc(const void* q, const void* Kg, const void* Vg, int64_t G,
                                 const void* K, const void* V, int n_shards, int Tq, int64_t S,
@@ -597,13 +619,16 @@ int pulsar_phase2_query_noalloc(const void* q, const void* Kg, const void* Vg, i
   const int chk = phase2_query_check(q, Kg, Vg, G, K, V, n_shards, Tq, S, Hq, Hkv, d,
                                      softmax_scale, o);
   if (chk != PULSAR_OK || Tq == 0) return chk;
-  const size_t need = pulsar_phase2_query_workspace_bytes(n_shards, Tq, S, G, Hq, Hkv, d);
-  if (need > (size_t)PULSAR_STATIC_SCRATCH_BYTES) return PULSAR_ETOOLARGE;
+  // longer key ranges, so fewer partials, where the scratch needs it
+  QueryPlan plan = query_plan(n_shards, Tq, S, G, Hq, Hkv, d, kDecodeMinKeys);
+  if (parts_bytes(plan, Tq, Hq, d) > (size_t)PULSAR_STATIC_SCRATCH_BYTES)
+    plan = query_plan(n_shards, Tq, S, G, Hq, Hkv, d, kDecodeMinKeysScarce);
+  if (parts_bytes(plan, Tq, Hq, d) > (size_t)PULSAR_STATIC_SCRATCH_BYTES) return PULSAR_ETOOLARGE;
   void* ws = nullptr;
   const int st = scratch_of_current_device(&ws);
   if (st != PULSAR_OK) return st;
-  return pulsar_phase2_query(q, Kg, Vg, G, K, V, n_shards, Tq, S, Hq, Hkv, d, softmax_scale, o,
-                             lse, ws, (size_t)PULSAR_STATIC_SCRATCH_BYTES, stream);
+  return phase2_query_run(plan, q, Kg, Vg, G, K, V, n_shards, Tq, S, Hq, Hkv, d, softmax_scale, o,
+                          lse, ws, stream);
 }
 
 }  // extern "C"

@@ -157,7 +157,9 @@ size_t maxidf_split_workspace(int batch, int64_t L, int num_blocks, int chunk, i
 int launch_maxidf_split(const int32_t* ids, int batch, int64_t L, int num_blocks, int chunk,
                         int topk, int vocab, int32_t* sel, int32_t* chunk_mindf, float* idf,
                         void* workspace, hipStream_t stream);
-int decode_parts(int n_shards, int64_t S, int Hkv);
+constexpr int kDecodeMinKeys = 32;        // one step of the decode kernel
+constexpr int kDecodeMinKeysScarce = 256;  // where partials have to be few
+int decode_parts(int n_shards, int64_t S, int Hkv, int min_keys = kDecodeMinKeys);
 bool decode_applies(int Tq, int Hq, int Hkv, int d);
 // The generation shard of a decode step, folded into the same launch: rows
 // [0, G) are the tokens appended earlier, row G + t is new token t's own, and

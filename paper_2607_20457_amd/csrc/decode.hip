@@ -30,6 +30,7 @@
 //      divided by the sum of those rounded weights, the LSE uses the fp32
 //      sum (as in the Phase-1 kernel).
 // The next step's K and V loads are in flight while a step is multiplied.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -325,18 +326,27 @@ void decode_attn_kernel(DecodeArgs a) {
 
 }  // namespace
 
+// Keys per range when S keys are cut into nparts ranges of whole 32-key steps.
+int decode_part_len(int64_t S, int nparts) {
+  const int64_t len = (S + nparts - 1) / nparts;
+  return (int)((len + DEC_KEYS - 1) / DEC_KEYS * DEC_KEYS);
+}
+
 // Key ranges per shard for the decode kernel: enough waves for one
 // four-wave workgroup per compute unit (as fast as two per compute unit,
-// measured, with half the partials to merge), at least 256 keys per range.
-int decode_parts(int n_shards, int64_t S, int Hkv) {
+// measured, with half the partials to merge), at least min_keys keys per
+// range.  With min_keys = kDecodeMinKeys (one step) a short context is cut
+// until the waves suffice or each has one step: such a call is bound by the
+// chain of dependent steps in a wave, not by bytes (one token over 4 x 1021
+// keys of 8 KV heads, d 128, with at least 256 / 128 / 64 / 32 keys per
+// range: 17.5 / 14.0 / 11.5 / 10.6 us for the launch and the merge).
+int decode_parts(int n_shards, int64_t S, int Hkv, int min_keys) {
   if (S <= 0 || n_shards <= 0 || Hkv <= 0) return 1;
   const int64_t waves = (int64_t)n_shards * Hkv;
   int64_t np = (256 * 4 + waves - 1) / waves;
-  const int64_t max_by_len = (S + 255) / 256;
-  if (np > max_by_len) np = max_by_len;
-  if (np < 1) np = 1;
-  if (np > 256) np = 256;
-  return (int)np;
+  np = std::min(std::min<int64_t>(np, (S + min_keys - 1) / min_keys), (int64_t)256);
+  const int64_t len = decode_part_len(S, (int)np);
+  return (int)((S + len - 1) / len);
 }
 
 bool decode_applies(int Tq, int Hq, int Hkv, int d) {
@@ -357,7 +367,7 @@ int launch_decode(const uint16_t* q, const uint16_t* K, const uint16_t* V, int n
   a.n_shards = n_shards;
   a.S = S;
   a.nparts = nparts;
-  a.part_len = (int)((S + nparts - 1) / nparts);
+  a.part_len = decode_part_len(S, nparts);
   a.tile_tokens = 32 / a.group;
   if (a.tile_tokens < 1) return PULSAR_EUNSUPPORTED;
   a.row_tiles = (Tq + a.tile_tokens - 1) / a.tile_tokens;
@@ -367,7 +377,7 @@ int launch_decode(const uint16_t* q, const uint16_t* K, const uint16_t* V, int n
     a.Vg = gen->V;
     a.G = (int)gen->G;
     a.gen_parts = gen->nparts;
-    a.gen_part_len = (int)((rows + gen->nparts - 1) / gen->nparts);
+    a.gen_part_len = decode_part_len(rows, gen->nparts);
   }
   a.scale_log2 = scale * 1.4426950408889634f;
   a.O = o;

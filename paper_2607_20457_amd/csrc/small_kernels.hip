@@ -140,55 +140,101 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(
   if (lse && dv == 0) lse[z * (int64_t)Hq * Tq + (int64_t)h * Tq + q] = ell;
 }
 
-// The same merge with one wavefront per output group of four values: lane
-// l folds parts l, l + 64, ..., and the wavefront combines the lanes.  For
-// few outputs and many parts (a decode step: 1024 outputs, tens to hundreds
-// of parts), where a thread per output leaves most of the chip idle and
-// walks the parts one after another.
-__global__ __launch_bounds__(256) void lse_merge_wide_kernel(
+// The same merge with one workgroup per output row (grid.y: DL groups of four
+// values of it), for few rows and many parts (a decode step: 32 rows, tens to
+// hundreds of parts).  Thread (pg, dv) folds parts pg, pg + PG, ... of one
+// group, CH of them with all their loads issued together, so a merge waits
+// for one round trip to memory where CH * PG covers the parts; then the
+// groups are folded across lanes and, through LDS, across wavefronts.
+template <int DL, int THREADS>
+__global__ __launch_bounds__(THREADS) void lse_merge_wide_kernel(
     const float* __restrict__ o_parts, const float* __restrict__ lse_parts, int H, int Tq, int Hq,
     int d4, int64_t part_ostride, int64_t part_lstride, float* __restrict__ o,
-    float* __restrict__ lse, int64_t total) {
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (i >= total) return;  // wave-uniform
-  const int dv = (int)(i % d4);
-  int64_t rest = i / d4;
-  const int h = (int)(rest % Hq);
-  rest /= Hq;
-  const int q = (int)(rest % Tq);
-  const int64_t z = rest / Tq;
+    float* __restrict__ lse) {
+  constexpr int PG = THREADS / DL;
+  constexpr int W = THREADS / 64;
+  constexpr int CH = 4;
+  __shared__ float s_m[W], s_s[W];
+  __shared__ f32x4 s_a[W][DL];
+  const int tid = threadIdx.x;
+  const int dv = blockIdx.y * DL + tid % DL;
+  const int pg = tid / DL;
+  const int64_t row = blockIdx.x;
+  const int h = (int)(row % Hq);
+  const int64_t zq = row / Hq;
+  const int q = (int)(zq % Tq);
+  const int64_t z = zq / Tq;
 
   const float* lp = lse_parts + z * (int64_t)H * part_lstride + (int64_t)h * Tq + q;
-  float mx = -INFINITY;
-  for (int p = lane; p < H; p += 64) mx = fmaxf(mx, lp[p * part_lstride]);
-  mx = wave_max(mx);
-  const int64_t orow = (((int64_t)q * Hq + h) * d4 + dv);
+  const int64_t orow = ((int64_t)q * Hq + h) * d4;
+  const f32x4* op = reinterpret_cast<const f32x4*>(o_parts) + z * (int64_t)H * (part_ostride / 4) +
+                    orow + min(dv, d4 - 1);
+  float m = -INFINITY, sum = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  float ell = -INFINITY;
-  if (mx != -INFINITY) {
-    float sum = 0.f;
-    for (int p = lane; p < H; p += 64) sum += __expf(lp[p * part_lstride] - mx);
+  for (int p0 = pg; p0 < H; p0 += CH * PG) {
+    float l[CH];
+    f32x4 v[CH];
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    ell = mx + __logf(sum);
-    const f32x4* op = reinterpret_cast<const f32x4*>(o_parts) + z * (int64_t)H * (part_ostride / 4);
-    for (int p = lane; p < H; p += 64) {
-      const float w = __expf(lp[p * part_lstride] - ell);
-      acc += w * op[p * (part_ostride / 4) + orow];
+    for (int u = 0; u < CH; ++u) {
+      const int p = min(p0 + u * PG, H - 1);  // a part past the last weighs zero
+      l[u] = lp[p * part_lstride];
+      v[u] = op[p * (part_ostride / 4)];
     }
+    float nm = m;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      acc.x += __shfl_xor(acc.x, off, 64);
-      acc.y += __shfl_xor(acc.y, off, 64);
-      acc.z += __shfl_xor(acc.z, off, 64);
-      acc.w += __shfl_xor(acc.w, off, 64);
+    for (int u = 0; u < CH; ++u)
+      if (p0 + u * PG < H) nm = fmaxf(nm, l[u]);
+    const float use = nm == -INFINITY ? 0.f : nm;  // no finite partial yet: weights 0
+    const float alpha = __expf(m - use);
+    sum *= alpha;
+    acc *= alpha;
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const float w = p0 + u * PG < H ? __expf(l[u] - use) : 0.f;
+      sum += w;
+      acc += w * v[u];
     }
+    m = nm;
   }
+  // lanes DL apart hold the same values' other parts
+#pragma unroll
+  for (int off = DL; off < 64; off <<= 1) {
+    const float m2 = __shfl_xor(m, off, 64);
+    const float nm = fmaxf(m, m2);
+    const float use = nm == -INFINITY ? 0.f : nm;
+    const float w1 = __expf(m - use), w2 = __expf(m2 - use);
+    sum = sum * w1 + __shfl_xor(sum, off, 64) * w2;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc[k] = acc[k] * w1 + __shfl_xor(acc[k], off, 64) * w2;
+    m = nm;
+  }
+  const int wave = tid >> 6, lane = tid & 63;
   if (lane == 0) {
-    reinterpret_cast<f32x4*>(o)[z * (int64_t)Tq * Hq * d4 + orow] = acc;
-    if (lse && dv == 0) lse[z * (int64_t)Hq * Tq + (int64_t)h * Tq + q] = ell;
+    s_m[wave] = m;
+    s_s[wave] = sum;
   }
+  if (lane < DL) s_a[wave][lane] = acc;
+  __syncthreads();
+  if (tid >= DL || dv >= d4) return;
+  m = s_m[0];
+#pragma unroll
+  for (int w = 1; w < W; ++w) m = fmaxf(m, s_m[w]);
+  const float use = m == -INFINITY ? 0.f : m;
+  sum = 0.f;
+  acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    const float e = __expf(s_m[w] - use);
+    sum += s_s[w] * e;
+    acc += s_a[w][tid] * e;
+  }
+  float ell = -INFINITY;
+  if (m != -INFINITY) {
+    ell = m + __logf(sum);
+    acc *= 1.f / sum;
+  }
+  reinterpret_cast<f32x4*>(o)[z * (int64_t)Tq * Hq * d4 + orow + dv] = acc;
+  if (lse && dv == 0) lse[z * (int64_t)Hq * Tq + (int64_t)h * Tq + q] = ell;
 }
 
 int launch_lse_merge(const float* o_parts, const float* lse_parts, int H, int nz, int Tq, int Hq,
@@ -196,11 +242,15 @@ int launch_lse_merge(const float* o_parts, const float* lse_parts, int H, int nz
                      hipStream_t stream) {
   const int64_t total = (int64_t)nz * Tq * Hq * (d / 4);
   if (total == 0) return PULSAR_OK;
-  if (H >= 8 && total <= 8192) {  // at most 32 workgroups of the per-output form
-    const int64_t blocks = (total + 3) / 4;
-    hipLaunchKernelGGL(lse_merge_wide_kernel, dim3((unsigned)blocks), dim3(256), 0, stream,
-                       o_parts, lse_parts, H, Tq, Hq, d / 4, part_ostride, part_lstride, o, lse,
-                       total);
+  const int64_t rows = (int64_t)nz * Tq * Hq;
+  // at most 32 workgroups of the per-output form, which leaves the chip idle
+  // and walks the parts one after another
+  if (H >= 8 && total <= 8192) {
+    const int dl = d <= 64 ? 16 : 32;
+    const dim3 grid((unsigned)rows, (unsigned)((d / 4 + dl - 1) / dl));
+    const auto wide = dl == 16 ? lse_merge_wide_kernel<16, 1024> : lse_merge_wide_kernel<32, 1024>;
+    hipLaunchKernelGGL(wide, grid, dim3(1024), 0, stream, o_parts, lse_parts, H, Tq, Hq, d / 4,
+                       part_ostride, part_lstride, o, lse);
     return hipGetLastError() == hipSuccess ? PULSAR_OK : PULSAR_EHIP;
   }
   const int64_t blocks = (total + 255) / 256;

@@ -131,6 +131,9 @@ def test_phase2_far_larger_later_score():
     (4, 5, 1000, 32, 4, 128),   # group 8: 32 packed rows
     (8, 1, 4100, 8, 2, 64),     # group 4, 32 packed rows, many key ranges
     (3, 4, 777, 8, 8, 128),     # group 1
+    (1, 4, 1021, 32, 8, 128),   # one 32-key step per range, the last of 29 keys
+    (1, 1, 64, 4, 1, 64),       # two ranges of one step
+    (1, 2, 8225, 4, 1, 128),    # 256 ranges asked for, of 64 keys each after rounding
 ])
 def test_decode_kernel_shapes(Tq, H, S, Hq, Hkv, d):
     # few query rows per KV head (Tq * Hq / Hkv <= 32): the decode kernel,
@@ -160,10 +163,15 @@ def test_decode_step_over_128k_shards_matches_dense():
     check_attention(o.cpu().numpy(), lse.cpu().numpy(), *ref, "decode over 128K")
 
 
-@pytest.mark.parametrize("H,Tq,Hq,d", [(8, 1, 32, 128), (258, 1, 32, 128), (70, 2, 8, 64)])
+@pytest.mark.parametrize("H,Tq,Hq,d", [
+    (8, 1, 32, 128), (258, 1, 32, 128), (70, 2, 8, 64),
+    (33, 1, 4, 4),      # one group of four values per row
+    (129, 3, 5, 72),    # a partial second slice of a row
+    (65, 1, 4, 260),    # three slices, the last of one group
+])
 def test_merge_many_parts_few_outputs(H, Tq, Hq, d):
-    # many partials, few outputs: the merge takes one wavefront per output
-    # group, its lanes over the parts; missing parts and large gaps included
+    # many partials, few outputs: the merge takes one workgroup per output
+    # row, its threads over the parts; missing parts and large gaps included
     rng = np.random.default_rng(H + Tq)
     op = rng.standard_normal((H, Tq, Hq, d)).astype(np.float32)
     lp = (rng.standard_normal((H, Hq, Tq)) * 30).astype(np.float32)

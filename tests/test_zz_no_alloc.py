@@ -66,3 +66,18 @@ def test_noalloc_rejects_partials_beyond_the_scratch():
     torch.cuda.synchronize()
     # the entry point still works afterwards
     _check(q, K, V, Kg, Vg, G=0, what="after a rejected call")
+
+
+def test_noalloc_takes_longer_key_ranges_where_the_scratch_needs_it():
+    # 100 short shards of 32 KV heads leave room for 127 partials of 32 rows:
+    # the generation shard's rows in 32-key ranges would take 32 more, in 256-key ranges 4
+    n, S, G, Tq, H, d = 100, 40, 980, 32, 32, 128
+    lib = P.api._lib.lib()
+    assert lib.pulsar_phase2_query_workspace_bytes(n, Tq, S, G, H, H, d) > (64 << 20)
+    q, K, V, Kg, Vg = _case(7301, n, S, G, Tq, H, H, d)
+    o, lse = P.phase2_query_noalloc(*(to_dev_bf16(x) for x in (q, Kg, Vg)), G,
+                                    *(to_dev_bf16(x) for x in (K, V)))
+    torch.cuda.synchronize()
+    o_ref, l_ref = attention.query_attention(f64(q), f64(K), f64(V), f64(Kg), f64(Vg), G,
+                                             1 / math.sqrt(d))
+    check_attention(o.cpu().numpy(), lse.cpu().numpy(), o_ref, l_ref, "few long ranges")
