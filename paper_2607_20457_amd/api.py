@@ -28,7 +28,9 @@ SCORE_ENTROPY = 3
 
 
 def _stream():
-    return int(torch.cuda.current_stream().cuda_stream)
+    # the current stream's handle without the Stream object around it (0.2
+    # against 2.9 us, of calls whose kernels take 10)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
@@ -59,13 +61,12 @@ def maxidf_summaries(ids: torch.Tensor, num_blocks: int, chunk: int, topk: int, 
     _need(ids, torch.int32, "ids")
     batch, L = ids.shape
     C = (L // num_blocks) // chunk if num_blocks > 0 and chunk > 0 else 0
-    dev = ids.device
-    sel = torch.empty((batch, num_blocks, topk), dtype=torch.int32, device=dev)
-    mindf = torch.empty((batch, num_blocks, C), dtype=torch.int32, device=dev) if return_mindf else None
-    idf = torch.empty((batch, vocab), dtype=torch.float32, device=dev) if return_idf else None
-    need = maxidf_workspace_bytes(batch, L, num_blocks, chunk, vocab) if num_blocks > 0 else 0
+    sel = ids.new_empty((batch, num_blocks, topk), dtype=torch.int32)
+    mindf = ids.new_empty((batch, num_blocks, C), dtype=torch.int32) if return_mindf else None
+    idf = ids.new_empty((batch, vocab), dtype=torch.float32) if return_idf else None
     if isinstance(workspace, str):
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev) if need else None
+        need = maxidf_workspace_bytes(batch, L, num_blocks, chunk, vocab) if num_blocks > 0 else 0
+        workspace = ids.new_empty(need, dtype=torch.uint8) if need else None
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = _lib.lib().pulsar_maxidf_summaries(_ptr(ids), batch, L, num_blocks, chunk, topk, vocab,
                                             _ptr(sel), _ptr(mindf), _ptr(idf), _ptr(workspace),
@@ -95,14 +96,13 @@ def chunk_summaries(ids: torch.Tensor, num_blocks: int, chunk: int, topk: int, v
     _need(ids, torch.int32, "ids")
     batch, L = ids.shape
     C = (L // num_blocks) // chunk if num_blocks > 0 and chunk > 0 else 0
-    dev = ids.device
-    sel = torch.empty((batch, num_blocks, topk), dtype=torch.int32, device=dev)
-    scores = torch.empty((batch, num_blocks, C), dtype=torch.float32, device=dev) \
+    sel = ids.new_empty((batch, num_blocks, topk), dtype=torch.int32)
+    scores = ids.new_empty((batch, num_blocks, C), dtype=torch.float32) \
         if return_scores else None
-    need = chunk_workspace_bytes(batch, L, num_blocks, chunk, vocab, scorer) \
-        if num_blocks > 0 else 0
     if isinstance(workspace, str):
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev) if need else None
+        need = chunk_workspace_bytes(batch, L, num_blocks, chunk, vocab, scorer) \
+            if num_blocks > 0 else 0
+        workspace = ids.new_empty(need, dtype=torch.uint8) if need else None
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = _lib.lib().pulsar_chunk_summaries(_ptr(ids), batch, L, num_blocks, chunk, topk, vocab,
                                            scorer, _ptr(sel), _ptr(scores), _ptr(workspace),
@@ -154,7 +154,7 @@ def phase1_gather(X, num_blocks: int, block_idx: int, sink: int, chunk: int, top
         _need(sel, torch.int32, "sel")
     b, L, H, d = X.shape
     n = phase1_len(L, num_blocks, block_idx, sink, chunk, topk, prefix_mode)
-    out = torch.empty((b, n, H, d), dtype=torch.bfloat16, device=X.device)
+    out = X.new_empty((b, n, H, d), dtype=torch.bfloat16)
     table = _freq_table(inv_freq, d)
     st = _lib.lib().pulsar_phase1_gather(_ptr(X), b, L, H, d, num_blocks, block_idx, sink, chunk,
                                          topk, _ptr(sel), prefix_mode, pos_mode,
@@ -181,19 +181,18 @@ def phase1_attn(Q, K, V, num_blocks: int, block_idx: int, sink: int, chunk: int,
         raise ValueError("K and V must be [batch, L, Hkv, d] matching Q")
     n = phase1_len(L, num_blocks, block_idx, sink, chunk, topk, prefix_mode)
     scale = 1.0 / math.sqrt(d) if softmax_scale is None else softmax_scale
-    dev = Q.device
     if out is not None:
         O = out
         _need(O, torch.bfloat16 if o_dtype == OUT_BF16 else torch.float32, "out")
         if O.shape != (b, n, Hq, d):
             raise ValueError("out has the wrong shape")
     else:
-        O = torch.empty((b, n, Hq, d), device=dev,
+        O = Q.new_empty((b, n, Hq, d),
                         dtype=torch.bfloat16 if o_dtype == OUT_BF16 else torch.float32)
-    lse = torch.empty((b, Hq, n), dtype=torch.float32, device=dev) if return_lse else None
+    lse = Q.new_empty((b, Hq, n), dtype=torch.float32) if return_lse else None
     Lb = L // num_blocks
-    Kk = torch.empty((b, Lb, Hkv, d), dtype=torch.bfloat16, device=dev) if keep_kv else None
-    Vk = torch.empty((b, Lb, Hkv, d), dtype=torch.bfloat16, device=dev) if keep_kv else None
+    Kk = Q.new_empty((b, Lb, Hkv, d), dtype=torch.bfloat16) if keep_kv else None
+    Vk = Q.new_empty((b, Lb, Hkv, d), dtype=torch.bfloat16) if keep_kv else None
     st = _lib.lib().pulsar_phase1_attn(_ptr(Q), _ptr(K), _ptr(V), b, L, Hq, Hkv, d, num_blocks,
                                        block_idx, sink, chunk, topk, _ptr(sel), prefix_mode,
                                        scale, _ptr(O), o_dtype, _ptr(lse), _ptr(Kk), _ptr(Vk),
@@ -222,12 +221,11 @@ def phase2_partial(q, K, V, softmax_scale: float | None = None, workspace=None):
     if dk != d or V.shape != K.shape:
         raise ValueError("K/V must be [n_shards, S, Hkv, d]")
     scale = 1.0 / math.sqrt(d) if softmax_scale is None else softmax_scale
-    dev = q.device
-    o = torch.empty((H, Tq, Hq, d), dtype=torch.float32, device=dev)
-    lse = torch.empty((H, Hq, Tq), dtype=torch.float32, device=dev)
+    o = q.new_empty((H, Tq, Hq, d), dtype=torch.float32)
+    lse = q.new_empty((H, Hq, Tq), dtype=torch.float32)
     need = phase2_workspace_bytes(H, Tq, S, Hq, Hkv, d)
     if need and (workspace is None or workspace.numel() * workspace.element_size() < need):
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+        workspace = q.new_empty(need, dtype=torch.uint8)
     st = _lib.lib().pulsar_phase2_partial(_ptr(q), _ptr(K), _ptr(V), H, Tq, S, Hq, Hkv, d, scale,
                                           _ptr(o), _ptr(lse), _ptr(workspace),
                                           need, _stream())
@@ -243,8 +241,8 @@ def lse_merge(o_parts, lse_parts):
     H, Tq, Hq, d = o_parts.shape
     if lse_parts.shape != (H, Hq, Tq):
         raise ValueError("lse_parts must be [H, Hq, Tq]")
-    o = torch.empty((Tq, Hq, d), dtype=torch.float32, device=o_parts.device)
-    lse = torch.empty((Hq, Tq), dtype=torch.float32, device=o_parts.device)
+    o = o_parts.new_empty((Tq, Hq, d), dtype=torch.float32)
+    lse = o_parts.new_empty((Hq, Tq), dtype=torch.float32)
     st = _lib.lib().pulsar_lse_merge(_ptr(o_parts), _ptr(lse_parts), H, Tq, Hq, d, _ptr(o),
                                      _ptr(lse), _stream())
     _lib.check(st, "pulsar_lse_merge")
@@ -292,12 +290,11 @@ def phase2_query(q, Kg, Vg, G: int, K=None, V=None, softmax_scale: float | None 
         if K.shape != (n_shards, S, Hkv, d) or V.shape != K.shape:
             raise ValueError("K/V must be [n_shards, S, Hkv, d]")
     scale = 1.0 / math.sqrt(d) if softmax_scale is None else softmax_scale
-    dev = q.device
-    o = torch.empty((Tq, Hq, d), dtype=torch.float32, device=dev)
-    lse = torch.empty((Hq, Tq), dtype=torch.float32, device=dev)
+    o = q.new_empty((Tq, Hq, d), dtype=torch.float32)
+    lse = q.new_empty((Hq, Tq), dtype=torch.float32)
     need = _lib.lib().pulsar_phase2_query_workspace_bytes(n_shards, Tq, S, G, Hq, Hkv, d)
     if workspace is None or workspace.numel() * workspace.element_size() < need:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
+        workspace = q.new_empty(max(need, 16), dtype=torch.uint8)
     st = _lib.lib().pulsar_phase2_query(_ptr(q), _ptr(Kg), _ptr(Vg), G, _ptr(K), _ptr(V), n_shards,
                                         Tq, S, Hq, Hkv, d, scale, _ptr(o), _ptr(lse),
                                         _ptr(workspace), need, _stream())
@@ -324,8 +321,8 @@ def phase2_query_noalloc(q, Kg, Vg, G: int, K=None, V=None, softmax_scale: float
         if K.shape != (n_shards, S, Hkv, d) or V.shape != K.shape:
             raise ValueError("K/V must be [n_shards, S, Hkv, d]")
     scale = 1.0 / math.sqrt(d) if softmax_scale is None else softmax_scale
-    o = torch.empty((Tq, Hq, d), dtype=torch.float32, device=q.device)
-    lse = torch.empty((Hq, Tq), dtype=torch.float32, device=q.device)
+    o = q.new_empty((Tq, Hq, d), dtype=torch.float32)
+    lse = q.new_empty((Hq, Tq), dtype=torch.float32)
     st = _lib.lib().pulsar_phase2_query_noalloc(_ptr(q), _ptr(Kg), _ptr(Vg), G, _ptr(K), _ptr(V),
                                                 n_shards, Tq, S, Hq, Hkv, d, scale, _ptr(o),
                                                 _ptr(lse), _stream())
