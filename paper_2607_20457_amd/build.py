@@ -27,6 +27,11 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 
+# Per source: a wave of the packed kernel may use more than 256 registers, and
+# by default every matrix instruction of such a function writes accumulation
+# registers, from which each score is copied back.
+SOURCE_FLAGS = {"packed.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+
 
 def sources():
     return sorted(glob.glob(os.path.join(HERE, "csrc", "*.hip")))
@@ -51,7 +56,8 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         objs = [os.path.join(tmpdir, os.path.basename(s) + ".o") for s in srcs]
         workers = max(1, min(len(srcs), os.cpu_count() or 1, 8))
         with cf.ThreadPoolExecutor(workers) as ex:
-            futs = [ex.submit(_run, [HIPCC, *FLAGS, *extra_flags, "-c", "-o", o, s], verbose)
+            futs = [ex.submit(_run, [HIPCC, *FLAGS, *SOURCE_FLAGS.get(os.path.basename(s), []),
+                                    *extra_flags, "-c", "-o", o, s], verbose)
                     for s, o in zip(srcs, objs)]
             for f in futs:
                 f.result()

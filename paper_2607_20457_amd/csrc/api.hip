@@ -268,9 +268,8 @@ int pulsar_phase1_attn(const void* Q, const void* K, const void* V, int batch, i
 // Phase-2 key splitting: each shard is cut into nsplit ranges so that the
 // launch has enough workgroups to cover the chip; the partials of a shard are
 // then merged with the same online-softmax merge as the shards themselves.
-static int phase2_splits(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d) {
+static int attn_splits(int n_shards, int Tq, int64_t S, int Hq, int Hkv) {
   if (S <= 0) return 1;
-  if (decode_applies(Tq, Hq, Hkv, d)) return decode_parts(n_shards, S, Hkv);
   const int group = Hq / Hkv;
   const int heads_per_wg = group >= 4 ? 4 : group;
   const int rows_per_wg = attn_rows_per_wg(group, false);
@@ -283,6 +282,13 @@ static int phase2_splits(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d
   if (ns < 1) ns = 1;
   if (ns > 64) ns = 64;
   return (int)ns;
+}
+
+static int phase2_splits(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d) {
+  if (S <= 0) return 1;
+  if (decode_applies(Tq, Hq, Hkv, d)) return decode_parts(n_shards, S, Hkv);
+  if (packed_applies(Tq, Hq, Hkv, d)) return packed_parts(n_shards, S, Hkv);
+  return attn_splits(n_shards, Tq, S, Hq, Hkv);
 }
 
 extern "C" {
@@ -314,9 +320,13 @@ int pulsar_phase2_partial(const void* q, const void* K, const void* V, int n_sha
     return PULSAR_EINVAL;
   int ns = phase2_splits(n_shards, Tq, S, Hq, Hkv, d);
   size_t need = pulsar_phase2_workspace_bytes(n_shards, Tq, S, Hq, Hkv, d);
-  // a few rows over short shards also run without a workspace, one wave per
-  // shard and KV head
-  if (workspace == nullptr && S <= 256 && decode_applies(Tq, Hq, Hkv, d)) {
+  // Short shards, or enough of them to fill the chip, also run without a
+  // workspace: one range per shard.
+  const bool decode = decode_applies(Tq, Hq, Hkv, d);
+  const bool packed = !decode && packed_applies(Tq, Hq, Hkv, d);
+  if (workspace == nullptr &&
+      ((decode && decode_parts(n_shards, S, Hkv, kDecodeMinKeysScarce) == 1) ||
+       (packed && attn_splits(n_shards, Tq, S, Hq, Hkv) == 1))) {
     ns = 1;
     need = 0;
   }
@@ -325,12 +335,13 @@ int pulsar_phase2_partial(const void* q, const void* K, const void* V, int n_sha
 
   float* ws_o = static_cast<float*>(workspace);
   float* ws_l = ws_o + (int64_t)n_shards * ns * Tq * Hq * d;
-  if (decode_applies(Tq, Hq, Hkv, d)) {
-    // few query rows: the decode kernel, one key range per wave
-    int st = launch_decode(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(K),
-                           static_cast<const uint16_t*>(V), n_shards, Tq, S, Hq, Hkv, d,
-                           softmax_scale, ns > 1 ? ws_o : o_parts, ns > 1 ? ws_l : lse_parts, ns,
-                           (hipStream_t)stream);
+  if (decode || packed) {
+    // few query rows: the decode kernel, one key range per wave, or the
+    // packed kernel, one per workgroup
+    int st = (decode ? launch_decode : launch_packed)(
+        static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(K),
+        static_cast<const uint16_t*>(V), n_shards, Tq, S, Hq, Hkv, d, softmax_scale,
+        ns > 1 ? ws_o : o_parts, ns > 1 ? ws_l : lse_parts, ns, (hipStream_t)stream, nullptr);
     if (st != PULSAR_OK || ns == 1) return st;
     return launch_lse_merge(ws_o, ws_l, ns, n_shards, Tq, Hq, d, (int64_t)Tq * Hq * d,
                             (int64_t)Hq * Tq, o_parts, lse_parts, (hipStream_t)stream);
@@ -382,9 +393,10 @@ int pulsar_lse_merge(const float* o_parts, const float* lse_parts, int H, int Tq
 namespace {
 inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 // Partials of a Phase-2 query step; every key range is its own partial and
-// one merge folds them all.  With the decode kernel (few query rows) one
-// launch covers the ranges of every shard and of the generation shard (the
-// G appended rows and the new tokens' own).  Otherwise the attention kernel
+// one merge folds them all.  With the decode kernel (few query rows) or the
+// packed kernel (a few dozen tokens) one launch covers the ranges of every
+// shard and of the generation shard (the G appended rows and the new tokens'
+// own).  Otherwise the attention kernel
 // gives the key splits of the shards.  A generation shard of at most
 // kGenDecodeRows rows, for at most kGenDecodeQueryRows (token, head) rows
 // per KV head, then goes to the decode kernel in 32-row tiles (each token
@@ -396,14 +408,34 @@ constexpr int64_t kGenDecodeRows = 4096;
 constexpr int64_t kGenDecodeQueryRows = 512;
 struct QueryPlan {
   bool decode;      // everything in one decode launch
+  bool packed;      // everything in one packed launch
   bool gen_decode;  // the generation shard in a decode launch
+  bool gen_own;     // the generation shard's ranges have partials of their own
   int np_shard, np_gen;  // key ranges per shard / of the generation shard's rows
   int parts;
 };
 QueryPlan query_plan(int n_shards, int Tq, int64_t S, int64_t G, int Hq, int Hkv, int d,
                      int min_keys) {
   QueryPlan p{};
+  p.gen_own = true;
   p.decode = decode_applies(Tq, Hq, Hkv, d);
+  p.packed = !p.decode && packed_applies(Tq, Hq, Hkv, d);
+  if (p.packed) {
+    // the generation shard in ranges about as long as the shards'
+    const int pk_keys = min_keys == kDecodeMinKeys ? kPackedMinKeys : kPackedMinKeysScarce;
+    p.np_shard = packed_parts(n_shards, S, Hkv, pk_keys);
+    // the generation shard in ranges about as long as the shards', in
+    // workgroups of their own while the chip has room for them, else as
+    // additions to the shards' ranges
+    const int64_t ranges = (int64_t)n_shards * p.np_shard, rows = G + Tq;
+    const int64_t len = n_shards > 0 ? (S + p.np_shard - 1) / p.np_shard : 0;
+    p.np_gen = packed_parts(1, rows, Hkv, (int)std::max<int64_t>(len, pk_keys));
+    p.gen_own = ranges == 0 || (ranges + p.np_gen) * Hkv <= 256;
+    if (!p.gen_own)
+      p.np_gen = (int)std::min<int64_t>(ranges, (rows + kPackedMinKeys - 1) / kPackedMinKeys);
+    p.parts = (int)ranges + (p.gen_own ? p.np_gen : 0);
+    return p;
+  }
   p.gen_decode = p.decode || ((d == 64 || d == 128) && Hq / Hkv <= 32 && G + Tq <= kGenDecodeRows &&
                                (int64_t)Tq * (Hq / Hkv) <= kGenDecodeQueryRows);
   if (p.decode) {
@@ -528,14 +560,15 @@ int phase2_query_run(const QueryPlan& plan, const void* q, const void* Kg, const
   float* pl = reinterpret_cast<float*>(static_cast<char*>(workspace) +
                                        align16((size_t)parts * ostride * 4));
   int part = 0, st = PULSAR_OK;
-  if (plan.decode) {
+  if (plan.decode || plan.packed) {
     // every key range its own partial, the shards' and then the generation
     // shard's, in one launch; then one merge
     const DecodeGen gen{static_cast<const uint16_t*>(Kg), static_cast<const uint16_t*>(Vg), G,
-                        plan.np_gen};
-    st = launch_decode(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(K),
-                       static_cast<const uint16_t*>(V), n_shards, Tq, S, Hq, Hkv, d,
-                       softmax_scale, po, pl, plan.np_shard, (hipStream_t)stream, &gen);
+                        plan.np_gen, plan.gen_own};
+    st = (plan.decode ? launch_decode : launch_packed)(
+        static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(K),
+        static_cast<const uint16_t*>(V), n_shards, Tq, S, Hq, Hkv, d, softmax_scale, po, pl,
+        plan.np_shard, (hipStream_t)stream, &gen);
     if (st != PULSAR_OK) return st;
     return launch_lse_merge(po, pl, parts, 1, Tq, Hq, d, ostride, lstride, o, lse,
                             (hipStream_t)stream);
@@ -548,7 +581,7 @@ int phase2_query_run(const QueryPlan& plan, const void* q, const void* Kg, const
   }
   if (plan.gen_decode) {  // the generation shard's rows, each token up to its own
     const DecodeGen gen{static_cast<const uint16_t*>(Kg), static_cast<const uint16_t*>(Vg), G,
-                        plan.np_gen};
+                        plan.np_gen, plan.gen_own};
     st = launch_decode(static_cast<const uint16_t*>(q), nullptr, nullptr, 0, Tq, 0, Hq, Hkv, d,
                        softmax_scale, po + part * ostride, pl + part * lstride, 1,
                        (hipStream_t)stream, &gen);

@@ -168,9 +168,21 @@ struct DecodeGen {
   const uint16_t* K;  // bf16 [G + Tq, Hkv, d]
   const uint16_t* V;
   int64_t G;
-  int nparts;         // key ranges (one partial each), after the shards' parts
+  int nparts;         // key ranges
+  // each range its own partial, after the shards' parts; otherwise (packed
+  // kernel only) range i joins the shards' part i
+  bool own;
 };
 int launch_decode(const uint16_t* q, const uint16_t* K, const uint16_t* V, int n_shards, int Tq,
+                  int64_t S, int Hq, int Hkv, int d, float scale, float* o, float* lse,
+                  int nparts, hipStream_t stream, const DecodeGen* gen = nullptr);
+// Phase-2 partials of a few dozen query rows per KV head (packed.hip), one
+// workgroup per key range; the generation shard's ranges as for launch_decode.
+constexpr int kPackedMinKeys = 128;        // one step of every wave
+constexpr int kPackedMinKeysScarce = 512;  // where partials have to be few
+bool packed_applies(int Tq, int Hq, int Hkv, int d);
+int packed_parts(int n_shards, int64_t S, int Hkv, int min_keys = kPackedMinKeys);
+int launch_packed(const uint16_t* q, const uint16_t* K, const uint16_t* V, int n_shards, int Tq,
                   int64_t S, int Hq, int Hkv, int d, float scale, float* o, float* lse,
                   int nparts, hipStream_t stream, const DecodeGen* gen = nullptr);
 int launch_scorer(const int32_t* ids, int batch, int64_t L, int num_blocks, int chunk, int topk,

@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(
 
 // The same merge with one workgroup per output row (grid.y: DL groups of four
 // values of it), for few rows and many parts (a decode step: 32 rows, tens to
-// hundreds of parts).  Thread (pg, dv) folds parts pg, pg + PG, ... of one
+// hundreds of parts; a query encoding: hundreds of rows, tens of parts).  Thread (pg, dv) folds parts pg, pg + PG, ... of one
 // group, CH of them with all their loads issued together, so a merge waits
 // for one round trip to memory where CH * PG covers the parts; then the
 // groups are folded across lanes and, through LDS, across wavefronts.
@@ -243,13 +243,19 @@ int launch_lse_merge(const float* o_parts, const float* lse_parts, int H, int nz
   const int64_t total = (int64_t)nz * Tq * Hq * (d / 4);
   if (total == 0) return PULSAR_OK;
   const int64_t rows = (int64_t)nz * Tq * Hq;
-  // at most 32 workgroups of the per-output form, which leaves the chip idle
-  // and walks the parts one after another
-  if (H >= 8 && total <= 8192) {
+  // One workgroup per row while the per-output form would have at most 160
+  // workgroups walking the parts one after another: of 1024 threads for up to
+  // 256 rows of 128 (a decode step: 3.6 against 5.1 us for 65 parts), of 256
+  // threads for up to 1280 (12 tokens, 33 parts: 3.3 against 5.3 us; 48 tokens:
+  // no difference, 64: 1 us slower).
+  if (H >= 8 && total <= 40960) {
     const int dl = d <= 64 ? 16 : 32;
     const dim3 grid((unsigned)rows, (unsigned)((d / 4 + dl - 1) / dl));
-    const auto wide = dl == 16 ? lse_merge_wide_kernel<16, 1024> : lse_merge_wide_kernel<32, 1024>;
-    hipLaunchKernelGGL(wide, grid, dim3(1024), 0, stream, o_parts, lse_parts, H, Tq, Hq, d / 4,
+    const int threads = total <= 8192 ? 1024 : 256;
+    const auto wide = threads == 1024
+                          ? (dl == 16 ? lse_merge_wide_kernel<16, 1024> : lse_merge_wide_kernel<32, 1024>)
+                          : (dl == 16 ? lse_merge_wide_kernel<16, 256> : lse_merge_wide_kernel<32, 256>);
+    hipLaunchKernelGGL(wide, grid, dim3(threads), 0, stream, o_parts, lse_parts, H, Tq, Hq, d / 4,
                        part_ostride, part_lstride, o, lse);
     return hipGetLastError() == hipSuccess ? PULSAR_OK : PULSAR_EHIP;
   }

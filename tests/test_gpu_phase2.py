@@ -185,3 +185,24 @@ def test_merge_many_parts_few_outputs(H, Tq, Hq, d):
     np.testing.assert_allclose(o.cpu().numpy(), ref_o, atol=1e-5, rtol=1e-5)
     np.testing.assert_allclose(lse.cpu().numpy(), ref_l, atol=1e-4, rtol=1e-6)
     assert np.all(o.cpu().numpy()[0, 0] == 0) and np.isneginf(lse.cpu().numpy()[0, 0])
+
+
+@pytest.mark.parametrize("Tq,S", [(1, 200), (20, 400)])
+def test_short_shards_need_no_workspace(Tq, S):
+    # one key range per shard where the caller brings no workspace, whatever
+    # ranges the call would be cut into with one
+    H, Hq, Hkv, d = 3, 32, 8, 128
+    q = workload.bf16_normal(61 + Tq, (Tq, Hq, d))
+    k, v = _shards(H, S, Hkv, d, 62 + S)
+    lib = P.api._lib.lib()
+    dq, dk, dv = to_dev_bf16(q), to_dev_bf16(k), to_dev_bf16(v)
+    o = torch.empty((H, Tq, Hq, d), device="cuda")
+    lse = torch.empty((H, Hq, Tq), device="cuda")
+    assert lib.pulsar_phase2_workspace_bytes(H, Tq, S, Hq, Hkv, d) > 0
+    assert lib.pulsar_phase2_partial(dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), H, Tq, S, Hq, Hkv,
+                                     d, 1 / math.sqrt(d), o.data_ptr(), lse.data_ptr(), None, 0,
+                                     P.api._stream()) == 0
+    torch.cuda.synchronize()
+    for h in range(H):
+        ref = attention.partial_attention(f64(q), f64(k[h]), f64(v[h]), 1 / math.sqrt(d))
+        check_attention(o[h].cpu().numpy(), lse[h].cpu().numpy(), *ref, f"shard {h}")

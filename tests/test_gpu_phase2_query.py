@@ -108,3 +108,42 @@ def test_few_rows_one_launch(Hq, Hkv, d, Tq, G, ns, S):
     v = workload.bf16_normal(seed + 4, (ns, S, Hkv, d)) if ns else None
     _run_and_check(q, kg, vg, G, k, v, f"few rows Hq={Hq} Hkv={Hkv} d={d} Tq={Tq} G={G} "
                    f"shards={ns}x{S}")
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,Tq,G,ns,S", [
+    (32, 8, 128, 9, 0, 2, 129),      # two row tiles, the second of 4 rows; a step past one range
+    (32, 8, 128, 16, 0, 1, 31),      # two full tiles, less than one step
+    (32, 8, 128, 17, 40, 3, 700),    # three tiles: the last tile group half empty
+    (32, 8, 128, 32, 0, 4, 1024),    # four full tiles, whole ranges
+    (24, 2, 128, 8, 3, 2, 200),      # 12 heads per KV head: tiles of 24 live rows
+    (64, 2, 128, 3, 500, 1, 90),     # 32 heads per KV head: one token per tile
+    (32, 8, 128, 20, 300, 32, 40),   # a full chip: the generation rows join the shards' ranges
+    (32, 8, 128, 20, 9000, 1, 5000), # long generation shard, ranges of its own
+    (16, 16, 64, 33, 0, 2, 127),     # d 64: two tiles, the second of one row
+    (16, 16, 64, 64, 7, 16, 65),     # d 64: two full tiles, generation rows joined
+    (16, 4, 64, 44, 10, 2, 640),     # d 64: six tiles, three per wave
+    (16, 4, 64, 37, 1000, 0, 0),     # d 64: five tiles, generation shard only
+])
+def test_packed_rows(Hq, Hkv, d, Tq, G, ns, S):
+    # a few dozen tokens: 32-row tiles of packed (token, head) rows
+    seed = 1300 + Hq + Tq + G
+    q = workload.bf16_normal(seed, (Tq, Hq, d))
+    kg = workload.bf16_normal(seed + 1, (G + Tq, Hkv, d))
+    vg = workload.bf16_normal(seed + 2, (G + Tq, Hkv, d))
+    k = workload.bf16_normal(seed + 3, (ns, S, Hkv, d)) if ns else None
+    v = workload.bf16_normal(seed + 4, (ns, S, Hkv, d)) if ns else None
+    _run_and_check(q, kg, vg, G, k, v, f"packed Hq={Hq} Hkv={Hkv} d={d} Tq={Tq} G={G} "
+                   f"shards={ns}x{S}")
+
+
+def test_packed_far_larger_later_score():
+    # one key far above every row's first scores (a weight sum past 2^88): the
+    # workgroup that holds it repeats its range with a raised reference
+    Tq, Hq, Hkv, d, S = 20, 8, 2, 128, 700
+    q = workload.bf16_bits_to_f32(workload.bf16_normal(1401, (Tq, Hq, d))) + 1.0
+    kf = workload.bf16_bits_to_f32(workload.bf16_normal(1402, (2, S, Hkv, d)))
+    kf[1, 400] = 8.0
+    qb, kb = workload.f32_to_bf16_bits(q), workload.f32_to_bf16_bits(kf)
+    vb = workload.bf16_normal(1403, (2, S, Hkv, d))
+    kg, vg = (workload.bf16_normal(s, (Tq, Hkv, d)) for s in (1404, 1405))
+    _run_and_check(qb, kg, vg, 0, kb, vb, "packed, far larger later score")
