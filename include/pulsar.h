@@ -114,9 +114,10 @@ int pulsar_version(void);
  * is read and only idf, when given, is written (ln(num_blocks) everywhere).
  * workspace   device buffer of at least pulsar_maxidf_workspace_bytes(...)
  *             bytes, 16-byte aligned, contents on entry irrelevant; or NULL.
- *             With it, a small batch runs in three launches split over the
- *             blocks and the vocabulary; with NULL (or a size query of 0) one
- *             workgroup takes each sequence.  The results are identical.
+ *             With it, a small batch of long sequences (or one whose IDF
+ *             table is wanted) runs in three launches split over the blocks
+ *             and the vocabulary; otherwise, and with NULL, each workgroup
+ *             counts a whole sequence.  The results are identical.
  * EWORKSPACE: a workspace smaller than the size query or misaligned.
  *
  * EINVAL: batch < 0, L < 0, num_blocks < 1, L % num_blocks != 0,
@@ -168,10 +169,10 @@ size_t pulsar_maxidf_workspace_bytes(int batch, int64_t L, int num_blocks, int c
  * scorer           a pulsar_scorer.
  * workspace        device buffer of at least pulsar_chunk_workspace_bytes(...)
  *                  bytes, 16-byte aligned, contents on entry irrelevant; or
- *                  NULL.  With it, a small batch runs split over the blocks
- *                  and the vocabulary (the Max-IDF split path's presence and
- *                  df launches, then one workgroup per block); with NULL (or
- *                  a size query of 0) one workgroup takes each sequence.  The
+ *                  NULL.  With it, a small batch of long sequences runs split
+ *                  over the blocks and the vocabulary (the Max-IDF split
+ *                  path's presence and df launches, then one workgroup per
+ *                  block); otherwise each workgroup counts a sequence.  The
  *                  scores agree bit for bit except where an fp64 sum taken
  *                  in another order rounds to the other side of an fp32
  *                  midpoint (one ulp), and the selections follow the scores.

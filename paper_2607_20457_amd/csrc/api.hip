@@ -111,8 +111,10 @@ int pulsar_maxidf_summaries(const int32_t* ids, int batch, int64_t L, int num_bl
   const size_t need = maxidf_split_workspace(batch, L, num_blocks, chunk, vocab);
   if (need > 0 && workspace != nullptr) {
     if (workspace_bytes < need || !aligned16(workspace)) return PULSAR_EWORKSPACE;
-    return launch_maxidf_split(ids, batch, L, num_blocks, chunk, topk, vocab, sel_chunks,
-                               chunk_mindf, idf, workspace, (hipStream_t)stream);
+    // (the IDF table is written by the whole chip only on the split path)
+    if (idf != nullptr || !maxidf_one_wg_pays(batch, L, num_blocks, chunk, vocab))
+      return launch_maxidf_split(ids, batch, L, num_blocks, chunk, topk, vocab, sel_chunks,
+                                 chunk_mindf, idf, workspace, (hipStream_t)stream);
   }
   const size_t lds = maxidf_lds_bytes(L, num_blocks, chunk, vocab);
   if (lds > PULSAR_LDS_BYTES) return PULSAR_EUNSUPPORTED;
@@ -153,8 +155,9 @@ int pulsar_chunk_summaries(const int32_t* ids, int batch, int64_t L, int num_blo
   const size_t need = pulsar_chunk_workspace_bytes(batch, L, num_blocks, chunk, vocab, scorer);
   if (need > 0 && workspace != nullptr) {
     if (workspace_bytes < need || !aligned16(workspace)) return PULSAR_EWORKSPACE;
-    return launch_scorer_split(ids, batch, L, num_blocks, chunk, topk, vocab, scorer, sel_chunks,
-                               chunk_scores, workspace, (hipStream_t)stream);
+    if (scorer_split_pays(batch, L, num_blocks, vocab, scorer))
+      return launch_scorer_split(ids, batch, L, num_blocks, chunk, topk, vocab, scorer, sel_chunks,
+                                 chunk_scores, workspace, (hipStream_t)stream);
   }
   return launch_scorer(ids, batch, L, num_blocks, chunk, topk, vocab, scorer, sel_chunks,
                        chunk_scores, (hipStream_t)stream);

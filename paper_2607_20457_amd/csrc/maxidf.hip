@@ -23,13 +23,15 @@
 //   * bitmaps (any N <= 255): a per-block bitmap, set with atomic OR; the
 //     lane that sets a bit first adds one to the id's df byte.
 //
-// Three kernels:
+// Four kernels:
 //   * resident (vocab <= 131072, L = 8192 times a power of two up to 16,
 //     blocks of a multiple of 8192 ids, hence N <= 16): stamp code (with df
 //     in the high nibble, see rstamp_tokens); pass 1 keeps every thread's
 //     ids (up to 128) in registers, packed, and pass 2 reads them back from
 //     there, so the ids cross HBM once; persistent over the batch, one
 //     workgroup per compute unit;
+//   * slots (N <= 16, up to 32 slots of 4096 ids, a whole number per block):
+//     the same with blocks of any length, see maxidf_slots_kernel;
 //   * streaming, stamp code (N <= 16, table and chunk minima fit in LDS):
 //     pass 2 streams the ids from HBM a second time;
 //   * streaming, bitmaps: compact layout (vocab <= 131072: a fixed 4096-word
@@ -38,7 +40,7 @@
 // A chunk's Max-IDF score ln(N / mindf) is strictly decreasing in mindf, so
 // ranking by (mindf ascending, index ascending) is ranking by (score
 // descending, index ascending).
-#include "summary.hpp"
+#include "split.hpp"
 
 
 static inline int64_t round_up4(int64_t x) { return (x + 3) & ~int64_t(3); }
@@ -74,7 +76,8 @@ enum MaxidfMode { kGeneral = 0, kCompact = 1, kStamp = 2 };
 
 struct MaxidfPlan {
   int mode;          // MaxidfMode of the streaming kernel
-  bool resident;     // stamp code with the ids held in registers
+  bool resident;     // stamp code with the ids held in registers, packed
+  int slots;         // stamp code with the ids held in this many slots (0: streamed)
   int64_t lds_bytes;
   int64_t cmin_off;  // byte offset of the chunk minima
 };
@@ -93,18 +96,29 @@ static MaxidfPlan maxidf_plan(int64_t L, int num_blocks, int chunk, int vocab) {
       res_rounds <= RES_ROUNDS &&
       (res_rounds & (res_rounds - 1)) == 0 && (L / num_blocks) % RES_ROUND_TOKENS == 0 &&
       chunk_bytes <= kResChunkBytes)
-    return {kStamp, true, PULSAR_LDS_BYTES, kFastVocab};
-  if (num_blocks <= kStampMaxBlocks && df_bytes + chunk_bytes <= PULSAR_LDS_BYTES)
-    return {kStamp, false, df_bytes + chunk_bytes, df_bytes};
+    return {kStamp, true, 0, PULSAR_LDS_BYTES, kFastVocab};
+  if (num_blocks <= kStampMaxBlocks && df_bytes + chunk_bytes <= PULSAR_LDS_BYTES) {
+    const int64_t slots = num_blocks * ((L / num_blocks + SLOT_TOKENS - 1) / SLOT_TOKENS);
+    const int64_t df16 = (df_bytes + 15) & ~int64_t(15);  // the table is cleared 16 bytes at a time
+    if (slots <= (vocab <= kFastVocab ? MAX_SLOTS : MAX_PLAIN_SLOTS) && df16 + chunk_bytes <= PULSAR_LDS_BYTES)
+      return {kStamp, false, (int)slots, df16 + chunk_bytes, df16};
+    return {kStamp, false, 0, df_bytes + chunk_bytes, df_bytes};
+  }
   if (vocab <= kFastVocab) {
     const bool in_bitmap = chunk_bytes <= kFastBitmapBytes;
     const int64_t lds = kFastBitmapBytes + df_bytes + (in_bitmap ? 0 : chunk_bytes);
     if (lds <= PULSAR_LDS_BYTES)
-      return {kCompact, false, lds, in_bitmap ? 0 : kFastBitmapBytes + df_bytes};
+      return {kCompact, false, 0, lds, in_bitmap ? 0 : kFastBitmapBytes + df_bytes};
   }
   const int64_t bitmap_bytes = bitmap_words(vocab) * 4;
-  return {kGeneral, false, df_bytes + (bitmap_bytes > chunk_bytes ? bitmap_bytes : chunk_bytes),
+  return {kGeneral, false, 0, df_bytes + (bitmap_bytes > chunk_bytes ? bitmap_bytes : chunk_bytes),
           df_bytes};
+}
+
+bool maxidf_one_wg_pays(int batch, int64_t L, int num_blocks, int chunk, int vocab) {
+  const MaxidfPlan plan = maxidf_plan(L, num_blocks, chunk, vocab);
+  return (plan.resident || plan.slots > 0) &&
+         !split_pays(PULSAR_SCORE_MAXIDF, batch, L, num_blocks, vocab);
 }
 
 size_t maxidf_lds_bytes(int64_t L, int num_blocks, int chunk, int vocab) {
@@ -324,38 +338,8 @@ __global__ __launch_bounds__(MAXIDF_THREADS) void maxidf_kernel(
   __syncthreads();
 
   // ---- select ------------------------------------------------------------
-  select_topk(cmin, b, num_blocks, Lb >> chunk_log2, (uint32_t)num_blocks, topk, sel, wave, lane);
-}
-
-// Stamp code of the resident kernel, block j: the high nibble of an id's byte
-// holds df - 1 and the low nibble the stamp 15 - j of the last block j it was
-// seen in; kStampNever (0xFF) before it is first seen.  The minimum of a
-// chunk's codes then carries the chunk's minimum df - 1 in its high nibble,
-// so pass 2 needs no conversion of the table.  A lane whose id is not yet
-// stamped with j writes (df - 1 + 1, 15 - j); as with stamp_tokens, every
-// writer of one byte during one block writes the same value.  CHECK_NEVER:
-// kStampNever carries the stamp of block 0 in its low nibble, so a round that
-// may belong to block 0 also tests for it.  nd: each id's df - 1 once this
-// block is counted (final in the last block).
-template <bool CHECK_NEVER>
-__device__ __forceinline__ void rstamp_tokens(const int (&t)[4], int j, uint8_t* code,
-                                              uint32_t (&nd)[4]) {
-  uint32_t c[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) c[i] = code[t[i]];
-  const uint32_t sj = 15u - (uint32_t)j;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const bool stamped = (c[i] & 15u) == sj && (!CHECK_NEVER || c[i] != kStampNever);
-    const uint32_t nc = ((c[i] + 16u) & 0xF0u) | sj;  // 0xFF + 16 wraps to df - 1 = 0
-    nd[i] = (stamped ? c[i] : nc) >> 4;
-    if (!stamped) code[t[i]] = (uint8_t)nc;
-  }
-}
-
-// df of a resident stamp code (0 for an id never seen)
-__device__ __forceinline__ uint32_t rstamp_df(uint32_t c) {
-  return c == kStampNever ? 0u : (c >> 4) + 1u;
+  select_topk(cmin, b, num_blocks, 0, num_blocks, Lb >> chunk_log2, (uint32_t)num_blocks, topk, sel,
+              wave, lane);
 }
 
 // Register-resident variant with the stamp code when the sequence fits the
@@ -577,9 +561,149 @@ __global__ __launch_bounds__(MAXIDF_THREADS) void maxidf_resident_kernel(
     // the next sequence's table is cleared while the select runs (it reads
     // only the chunk minima)
     if (b + gridDim.x < batch) clear_table();
-    select_topk(cmin, b, num_blocks, (int)(L / num_blocks) >> chunk_log2, (uint32_t)num_blocks, topk,
-                sel, wave, lane);
+    select_topk(cmin, b, num_blocks, 0, num_blocks, (int)(L / num_blocks) >> chunk_log2,
+                (uint32_t)num_blocks, topk, sel, wave, lane);
   }
+}
+
+// Slot variant: blocks of any length whose slots (4 consecutive ids per
+// thread, ceil(Lb / 4096) slots per block) fit in registers, N <= 16.  The
+// loads are issued before the table is cleared, each block is stamped from
+// its registers with the code of the resident kernel, and pass 2 reads the ids
+// back from there: the ids cross HBM once and no block waits for its loads.
+// A wavefront past its block's ids skips the slot.  The streaming kernel,
+// bound by the two rounds of loads it has in flight, by padding every block to
+// 8192 ids and by its conversion of the table, takes about twice as long: 256
+// sequences of 8 x 4096 ids 16.7 us (2.0 TB/s), 9.0 us here; 512 of 4 x 1024
+// ids 17.8, 8.6 us; 32 of 16 x 4096 ids 26.7, 15.8 us.
+//
+// Up to 16 slots keep their ids as loaded, all loads in flight at once; 32
+// (PACK) as in the resident kernel (17 bits an id), with RING slots in flight
+// (32 sequences of 12 x 4928 ids: streamed 22.6 us, 18.0 us here).  The
+// resident kernel's shortcuts for the first and last block changed nothing
+// here (within 3 %).
+template <int SL, int GL, bool PACK>
+__global__ __launch_bounds__(MAXIDF_THREADS) void maxidf_slots_kernel(
+    const int32_t* __restrict__ ids, int64_t L, int num_blocks, int Lb, int slots_per_block,
+    int part_blocks, int chunk_log2, int topk, int vocab, int cmin_off, int32_t* __restrict__ sel,
+    int32_t* __restrict__ chunk_mindf, float* __restrict__ idf) {
+  constexpr int RING = PACK ? 8 : SL;
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t b = blockIdx.x;
+  // the blocks this workgroup selects from
+  const int j0 = blockIdx.y * part_blocks, j1 = min(num_blocks, j0 + part_blocks);
+  uint8_t* const code8 = reinterpret_cast<uint8_t*>(lds);
+  uint8_t* const cmin = code8 + cmin_off;
+  const uint32_t vmax = (uint32_t)(vocab - 1);
+  const int nslots = num_blocks * slots_per_block;
+  const int nvec = Lb >> 2;  // groups of 4 ids per block
+  const int cl2 = GL >= 0 ? GL + 2 : chunk_log2;
+  const int C = Lb >> cl2;
+
+  const __amdgpu_buffer_rsrc_t rsrc = seq_resource(ids + b * L, L);
+  auto step = [&](SlotPos& p) { p.step(slots_per_block); };
+  u32x4 x[RING];
+  SlotPos pl;  // of the next load
+  auto load = [&](int s) {
+    x[s % RING] = load_slot(rsrc, s < nslots, pl, Lb, L, tid);
+    step(pl);
+  };
+#pragma unroll
+  for (int s = 0; s < RING; ++s) load(s);
+  {
+    const u32x4 never = {kStampNever * 0x01010101u, kStampNever * 0x01010101u,
+                         kStampNever * 0x01010101u, kStampNever * 0x01010101u};
+    const int n16 = (vocab + 15) >> 4;
+    u32x4* const t16 = reinterpret_cast<u32x4*>(lds);
+    for (int w = tid; w < n16; w += MAXIDF_THREADS) t16[w] = never;
+  }
+
+  // ---- pass 1 ----------------------------------------------------------------
+  uint32_t plo[PACK ? SL : 1][2];               // low 16 bits, two ids per register
+  uint32_t hb[PACK ? (SL + 7) / 8 : 1] = {};    // bit 16 of slot s: bit s % 8 of byte i
+  SlotPos p;
+#pragma unroll
+  for (int s = 0; s < SL; ++s, step(p)) {
+    if (s < nslots && p.r == 0) __syncthreads();  // everyone is done with the previous block
+    u32x4& xs = x[s % RING];
+    if (s < nslots && p.r * MAXIDF_THREADS + wave * 64 < nvec) {  // wave-uniform
+#pragma unroll
+      for (int i = 0; i < 4; ++i) xs[i] = clamp_id(xs[i], vmax);
+      if constexpr (PACK) {
+        plo[s][0] = __builtin_amdgcn_perm(xs[1], xs[0], 0x05040100u);
+        plo[s][1] = __builtin_amdgcn_perm(xs[3], xs[2], 0x05040100u);
+        hb[s >> 3] |= (__builtin_amdgcn_perm(xs[1], xs[0], 0x0C0C0602u) |
+                       (__builtin_amdgcn_perm(xs[3], xs[2], 0x0C0C0602u) << 16))
+                      << (s & 7);
+      }
+      if (p.r * MAXIDF_THREADS + tid < nvec) {
+        const int t[4] = {(int)xs[0], (int)xs[1], (int)xs[2], (int)xs[3]};
+        uint32_t nd[4];
+        rstamp_tokens<true>(t, p.j, code8, nd);
+      }
+    }
+    if constexpr (PACK) {
+      asm volatile("" : "+v"(plo[s][0]), "+v"(plo[s][1]), "+v"(hb[s >> 3]));
+      if (s + RING < SL) load(s + RING);
+    }
+  }
+  __syncthreads();
+  if (idf) {  // each part writes its share of the table
+    const float nb = (float)num_blocks;
+    float* out = idf + b * vocab;
+    for (int t = blockIdx.y * MAXIDF_THREADS + tid; t < vocab; t += gridDim.y * MAXIDF_THREADS) {
+      const uint32_t d = rstamp_df(code8[t]);
+      out[t] = logf(nb / (float)(d > 1u ? d : 1u));
+    }
+  }
+
+  // ---- pass 2: per-chunk minimum df from the registers --------------------
+  const int lg = cl2 - 2;  // log2 of the lanes per chunk
+  p = SlotPos{};
+#pragma unroll
+  for (int s = 0; s < SL; ++s, step(p)) {
+    const int g = p.r * MAXIDF_THREADS + tid;
+    if (p.j >= j0 && p.j < j1 && p.r * MAXIDF_THREADS + wave * 64 < nvec) {  // wave-uniform
+      // a lane past the block works on ids of its own and records nothing
+      uint32_t t[4];
+      if constexpr (PACK) {
+        const uint32_t h = (hb[s >> 3] >> (s & 7)) & 0x01010101u;
+        t[0] = __builtin_amdgcn_perm(h, plo[s][0], 0x0C040100u);
+        t[1] = __builtin_amdgcn_perm(h, plo[s][0], 0x0C050302u);
+        t[2] = __builtin_amdgcn_perm(h, plo[s][1], 0x0C060100u);
+        t[3] = __builtin_amdgcn_perm(h, plo[s][1], 0x0C070302u);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t[i] = x[s][i];
+      }
+      uint32_t mn = min(min((uint32_t)code8[t[0]], (uint32_t)code8[t[1]]),
+                        min((uint32_t)code8[t[2]], (uint32_t)code8[t[3]])) >> 4;
+      if constexpr (GL >= 0) mn = group_min_c<GL>(mn);
+      else mn = group_min(mn, 1 << lg);
+      mn += 1u;
+      if (g < nvec && (tid & ((1 << lg) - 1)) == 0) {
+        const int c = p.j * C + (g >> lg);
+        cmin[c] = (uint8_t)mn;
+        if (chunk_mindf) chunk_mindf[b * num_blocks * C + c] = (int32_t)mn;
+      }
+    }
+  }
+  __syncthreads();
+  select_topk(cmin, b, num_blocks, j0, j1, C, (uint32_t)num_blocks, topk, sel, wave, lane);
+}
+
+typedef void (*SlotsKernel)(const int32_t*, int64_t, int, int, int, int, int, int, int, int,
+                            int32_t*, int32_t*, float*);
+template <int SL>
+static SlotsKernel slots_for_chunk(int chunk_log2) {
+  constexpr bool PACK = SL > 16;
+  if (chunk_log2 == 4) return maxidf_slots_kernel<SL, 2, PACK>;
+  if (chunk_log2 == 5) return maxidf_slots_kernel<SL, 3, PACK>;
+  if (chunk_log2 == 6) return maxidf_slots_kernel<SL, 4, PACK>;
+  return maxidf_slots_kernel<SL, -1, PACK>;
 }
 
 // Resident kernels by (rounds, chunk): the lane group is a template argument
@@ -635,6 +759,21 @@ int launch_maxidf(const int32_t* ids, int batch, int64_t L, int num_blocks, int 
     if (kern == nullptr) return PULSAR_EINVAL;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(MAXIDF_THREADS), 0, stream, ids, batch, num_blocks,
                        rpb_log2, chunk_log2, topk, vocab, sel, chunk_mindf, idf);
+    return hipGetLastError() == hipSuccess ? PULSAR_OK : PULSAR_EHIP;
+  }
+  if (plan.slots > 0) {
+    const SlotsKernel kern = plan.slots <= 4   ? slots_for_chunk<4>(chunk_log2)
+                             : plan.slots <= 8 ? slots_for_chunk<8>(chunk_log2)
+                             : plan.slots <= 16 ? slots_for_chunk<16>(chunk_log2)
+                                                : slots_for_chunk<32>(chunk_log2);
+    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds_bytes) != hipSuccess)
+      return PULSAR_EHIP;
+    const int per = blocks_per_part(batch, num_blocks);
+    hipLaunchKernelGGL(kern, dim3(batch, (num_blocks + per - 1) / per), dim3(MAXIDF_THREADS),
+                       lds_bytes, stream, ids, L, num_blocks, (int)(L / num_blocks),
+                       plan.slots / num_blocks, per, chunk_log2, topk, vocab, (int)plan.cmin_off,
+                       sel, chunk_mindf, idf);
     return hipGetLastError() == hipSuccess ? PULSAR_OK : PULSAR_EHIP;
   }
   const auto kern = plan.mode == kStamp     ? maxidf_kernel<kStamp>

@@ -3,9 +3,12 @@
 // (Eq. entropy), and Max-IDF again (Eq. maxidf) so that every scorer has the
 // same interface.  They share the document-frequency pass with Max-IDF.
 //
-// One 1024-thread workgroup per sequence, N <= 16 blocks:
-//   pass 1  the stamp-code df table in LDS (summary.hpp), then df - 1 per id;
-//   pass 2  the ids streamed again, 4 per lane; the lanes of a chunk (chunk/4
+// 1024-thread workgroups, one per sequence or, for a batch of fewer than 128,
+// several that share its blocks (summary.hpp), N <= 16 blocks:
+//   pass 1  the stamp-code df table in LDS (summary.hpp), from ids held in
+//           registers (up to MAX_PLAIN_SLOTS slots; BM25 of 128 x 8 x 2048
+//           ids 24.5 -> 18.1 us) or streamed, then df - 1 per id;
+//   pass 2  the part's ids, 4 per lane; the lanes of a chunk (chunk/4
 //           of them) each add up their 4 positions and combine with
 //           cross-lane operations;
 //   select  the k best chunks of each block in positional order.
@@ -91,12 +94,12 @@ __device__ __forceinline__ T group_sum(T x, int group) {
   return x;
 }
 
-template <int SCORER, int GL>
+template <int SCORER, int GL, int SL>
 __global__ __launch_bounds__(MAXIDF_THREADS) void scorer_kernel(
     const int32_t* __restrict__ ids, int64_t L, int num_blocks, int Lb, int chunk_log2, int topk,
-    int vocab, int key_off, int tab_off, int stage_off, int32_t* __restrict__ sel,
-    float* __restrict__ scores) {
-  extern __shared__ uint32_t lds[];
+    int vocab, int key_off, int tab_off, int stage_off, int slots_per_block,
+    int part_blocks, int32_t* __restrict__ sel, float* __restrict__ scores) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
   uint8_t* const lds8 = reinterpret_cast<uint8_t*>(lds);
   uint8_t* code8 = lds8;
   uint32_t* keys = reinterpret_cast<uint32_t*>(lds8 + key_off);
@@ -104,8 +107,10 @@ __global__ __launch_bounds__(MAXIDF_THREADS) void scorer_kernel(
   double* tab_tf = tab_df + num_blocks + 1;                     // [m + 1] by tf
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t b = blockIdx.x;
+  // the blocks this workgroup scores
+  const int j0 = blockIdx.y * part_blocks, j1 = min(num_blocks, j0 + part_blocks);
   const int m = 1 << chunk_log2;
   const int group_log2 = GL >= 0 ? GL : chunk_log2 - 2;  // lanes per chunk: 1..64
   const int group = 1 << group_log2;
@@ -114,7 +119,25 @@ __global__ __launch_bounds__(MAXIDF_THREADS) void scorer_kernel(
   const int4* seq4 = reinterpret_cast<const int4*>(ids + b * L);
   const double N = (double)num_blocks;
 
-  for (int w = tid; w < vocab_w4; w += MAXIDF_THREADS) lds[w] = kStampNever * 0x01010101u;
+  // SL > 0: every id is loaded up front and stays in registers
+  constexpr int NX = SL > 0 ? SL : 1;
+  const int nslots = num_blocks * slots_per_block;
+  const int nvec = Lb >> 2;  // groups of 4 ids per block
+  u32x4 x[NX];
+  if constexpr (SL > 0) {
+    const __amdgpu_buffer_rsrc_t rsrc = seq_resource(ids + b * L, L);
+    SlotPos p;
+#pragma unroll
+    for (int s = 0; s < SL; ++s, p.step(slots_per_block))
+      x[s] = load_slot(rsrc, s < nslots, p, Lb, L, tid);
+  }
+  {
+    // up to the chunk keys, which start 16-byte aligned behind the table
+    const u32x4 never = {kStampNever * 0x01010101u, kStampNever * 0x01010101u,
+                         kStampNever * 0x01010101u, kStampNever * 0x01010101u};
+    u32x4* const t16 = reinterpret_cast<u32x4*>(lds);
+    for (int w = tid; w < key_off >> 4; w += MAXIDF_THREADS) t16[w] = never;
+  }
   // per-value tables (the first barrier of pass 1 orders them)
   if (tid <= num_blocks) {
     const double d = (double)tid;
@@ -129,26 +152,36 @@ __global__ __launch_bounds__(MAXIDF_THREADS) void scorer_kernel(
   }
 
   // ---- pass 1: document frequency ----------------------------------------
-  stamp_pass_streaming(seq4, num_blocks, Lb, vmax, code8, tid);
-  stamp_to_df(lds, vocab_w4, tid);
+  if constexpr (SL > 0) {
+    SlotPos p;
+#pragma unroll
+    for (int s = 0; s < SL; ++s, p.step(slots_per_block)) {
+      if (s < nslots && p.r == 0) __syncthreads();  // everyone is done with the previous block
+      if (s < nslots && p.r * MAXIDF_THREADS + tid < nvec) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[s][i] = clamp_id(x[s][i], vmax);
+        const int t[4] = {(int)x[s][0], (int)x[s][1], (int)x[s][2], (int)x[s][3]};
+        uint32_t nd[4];
+        rstamp_tokens<true>(t, p.j, code8, nd);
+      }
+    }
+  } else {
+    stamp_pass_streaming(seq4, num_blocks, Lb, vmax, code8, tid);
+    stamp_to_df(lds, vocab_w4, tid);
+  }
   __syncthreads();
 
   // ---- pass 2: per-chunk score and key --------------------------------------
-  const int nvec_seq = (int)(L >> 2);
-  const int n_iter = (nvec_seq + MAXIDF_THREADS - 1) / MAXIDF_THREADS;
   const int nchunks_seq = (int)(L >> chunk_log2);
   int4* stage = reinterpret_cast<int4*>(lds8 + stage_off) + wave * 64;
   const int gbase = lane & ~(group - 1);  // first lane of this lane's chunk
-  // the next iteration's ids load while this one is scored; past the end a
-  // lane re-reads the last group (without a branch), which it does not use
-  auto load_it = [&](int it) { return seq4[min(it * MAXIDF_THREADS + tid, nvec_seq - 1)]; };
-  auto body = [&](int it, const int4 x4) {
-    const int v = it * MAXIDF_THREADS + tid;
-    auto clamp = [&](int x) { return (uint32_t)x < vmax ? (uint32_t)x : vmax; };
-    const uint32_t t[4] = {clamp(x4.x), clamp(x4.y), clamp(x4.z), clamp(x4.w)};
+  // this lane's four ids; c: their chunk, recorded by its first lane if `ok`
+  auto body = [&](const u32x4 x4, bool ok, int c) {
+    const uint32_t t[4] = {clamp_id(x4[0], vmax), clamp_id(x4[1], vmax), clamp_id(x4[2], vmax),
+                           clamp_id(x4[3], vmax)};
     uint32_t dfm1[4];  // df - 1
 #pragma unroll
-    for (int i = 0; i < 4; ++i) dfm1[i] = code8[t[i]];
+    for (int i = 0; i < 4; ++i) dfm1[i] = SL > 0 ? code8[t[i]] >> 4 : code8[t[i]];
     uint32_t key = 0;
     float score = 0.f;
     if constexpr (SCORER == PULSAR_SCORE_MAXIDF) {
@@ -200,20 +233,46 @@ __global__ __launch_bounds__(MAXIDF_THREADS) void scorer_kernel(
         key = (uint32_t)(m - distinct);
       }
     }
-    if ((lane & (group - 1)) == 0 && v < nvec_seq) {
-      const int c = v >> group_log2;
+    if ((lane & (group - 1)) == 0 && ok) {
       keys[c] = key;
       if (scores) scores[b * nchunks_seq + c] = score;
     }
   };
-  // unrolled by two, so that each buffer keeps its register while its load
-  // is in flight (the same trip count in every lane)
-  int4 xa = load_it(0), xb = load_it(1);
-  for (int it = 0; it < n_iter; it += 2) {
-    body(it, xa);
-    xa = load_it(it + 2);
-    if (it + 1 < n_iter) body(it + 1, xb);
-    xb = load_it(it + 3);
+  // The scorers that count tf read the ids again (from L2, as a loop): with
+  // their comparisons unrolled over the slots the kernel outgrows the
+  // instruction cache (16 x 256 ids a block, BM25: 30.7 us).
+  constexpr bool TF = SCORER == PULSAR_SCORE_BM25 || SCORER == PULSAR_SCORE_ENTROPY;
+  if constexpr (SL > 0 && !TF) {
+    const int C = Lb >> chunk_log2;
+    SlotPos p;
+#pragma unroll
+    for (int s = 0; s < SL; ++s, p.step(slots_per_block)) {
+      const int g = p.r * MAXIDF_THREADS + tid;
+      if (p.j >= j0 && p.j < j1 && p.r * MAXIDF_THREADS + wave * 64 < nvec)  // wave-uniform
+        body(x[s], g < nvec, p.j * C + (g >> group_log2));
+    }
+  } else {
+    // The next iteration's ids load while this one is scored; past the end a
+    // lane re-reads the last group (without a branch), which it does not use.
+    // Unrolled by two, so that each buffer keeps its register while its load
+    // is in flight (the same trip count in every lane).
+    const int v0 = j0 * nvec, v1 = j1 * nvec;  // groups of 4 ids of the part
+    const int n_iter = (v1 - v0 + MAXIDF_THREADS - 1) / MAXIDF_THREADS;
+    auto load_it = [&](int it) {
+      const int4 q = seq4[min(v0 + it * MAXIDF_THREADS + tid, v1 - 1)];
+      return u32x4{(uint32_t)q.x, (uint32_t)q.y, (uint32_t)q.z, (uint32_t)q.w};
+    };
+    auto run = [&](int it, const u32x4 q) {
+      const int v = v0 + it * MAXIDF_THREADS + tid;
+      body(q, v < v1, v >> group_log2);
+    };
+    u32x4 xa = load_it(0), xb = load_it(1);
+    for (int it = 0; it < n_iter; it += 2) {
+      run(it, xa);
+      xa = load_it(it + 2);
+      if (it + 1 < n_iter) run(it + 1, xb);
+      xb = load_it(it + 3);
+    }
   }
   __syncthreads();
 
@@ -221,7 +280,7 @@ __global__ __launch_bounds__(MAXIDF_THREADS) void scorer_kernel(
   const uint32_t key_hi = SCORER == PULSAR_SCORE_MAXIDF   ? (uint32_t)num_blocks
                           : SCORER == PULSAR_SCORE_ENTROPY ? (uint32_t)m
                                                            : 0xFFFFFFFFu;
-  select_topk(keys, b, num_blocks, Lb >> chunk_log2, key_hi, topk, sel, wave, lane);
+  select_topk(keys, b, num_blocks, j0, j1, Lb >> chunk_log2, key_hi, topk, sel, wave, lane);
 }
 
 // ---- split path: a small batch over many compute units ----------------------
@@ -413,14 +472,21 @@ __global__ __launch_bounds__(kSplitThreads) void split_score_kernel(
   }
 }
 
-typedef void (*ScorerKernel)(const int32_t*, int64_t, int, int, int, int, int, int, int, int,
-                             int32_t*, float*);
+typedef void (*ScorerKernel)(const int32_t*, int64_t, int, int, int, int, int, int, int, int, int,
+                             int, int32_t*, float*);
 
-template <int SCORER>
+template <int SCORER, int SL>
 ScorerKernel scorer_for_chunk(int chunk_log2) {
-  if (chunk_log2 == 5) return scorer_kernel<SCORER, 3>;
-  if (chunk_log2 == 4) return scorer_kernel<SCORER, 2>;
-  return scorer_kernel<SCORER, -1>;
+  if (chunk_log2 == 5) return scorer_kernel<SCORER, 3, SL>;
+  if (chunk_log2 == 4) return scorer_kernel<SCORER, 2, SL>;
+  return scorer_kernel<SCORER, -1, SL>;
+}
+// slots: of the sequence (above MAX_PLAIN_SLOTS its ids are streamed)
+template <int SCORER>
+ScorerKernel scorer_for(int chunk_log2, int slots) {
+  return slots <= 8                 ? scorer_for_chunk<SCORER, 8>(chunk_log2)
+         : slots <= MAX_PLAIN_SLOTS ? scorer_for_chunk<SCORER, MAX_PLAIN_SLOTS>(chunk_log2)
+                                    : scorer_for_chunk<SCORER, 0>(chunk_log2);
 }
 
 }  // namespace
@@ -435,25 +501,33 @@ int launch_scorer(const int32_t* ids, int batch, int64_t L, int num_blocks, int 
   int chunk_log2 = 0;
   while ((1 << chunk_log2) < chunk) ++chunk_log2;
   const ScorerLayout lay = scorer_layout(L, num_blocks, chunk, vocab, scorer);
+  const int spb = (int)((L / num_blocks + SLOT_TOKENS - 1) / SLOT_TOKENS);
+  const int slots = num_blocks * spb;
   ScorerKernel kern = nullptr;
   switch (scorer) {
-    case PULSAR_SCORE_MAXIDF: kern = scorer_for_chunk<PULSAR_SCORE_MAXIDF>(chunk_log2); break;
-    case PULSAR_SCORE_TFIDF: kern = scorer_for_chunk<PULSAR_SCORE_TFIDF>(chunk_log2); break;
-    case PULSAR_SCORE_BM25: kern = scorer_for_chunk<PULSAR_SCORE_BM25>(chunk_log2); break;
-    case PULSAR_SCORE_ENTROPY: kern = scorer_for_chunk<PULSAR_SCORE_ENTROPY>(chunk_log2); break;
+    case PULSAR_SCORE_MAXIDF: kern = scorer_for<PULSAR_SCORE_MAXIDF>(chunk_log2, slots); break;
+    case PULSAR_SCORE_TFIDF: kern = scorer_for<PULSAR_SCORE_TFIDF>(chunk_log2, slots); break;
+    case PULSAR_SCORE_BM25: kern = scorer_for<PULSAR_SCORE_BM25>(chunk_log2, slots); break;
+    case PULSAR_SCORE_ENTROPY: kern = scorer_for<PULSAR_SCORE_ENTROPY>(chunk_log2, slots); break;
     default: return PULSAR_EINVAL;
   }
   if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)lay.bytes) != hipSuccess)
     return PULSAR_EHIP;
-  hipLaunchKernelGGL(kern, dim3(batch), dim3(MAXIDF_THREADS), (size_t)lay.bytes, stream, ids, L,
+  const int per = blocks_per_part(batch, num_blocks);
+  hipLaunchKernelGGL(kern, dim3(batch, (num_blocks + per - 1) / per), dim3(MAXIDF_THREADS),
+                     (size_t)lay.bytes, stream, ids, L,
                      num_blocks, (int)(L / num_blocks), chunk_log2, topk, vocab,
-                     (int)lay.key_off, (int)lay.tab_off, (int)lay.stage_off, sel, scores);
+                     (int)lay.key_off, (int)lay.tab_off, (int)lay.stage_off, spb, per, sel, scores);
   return hipGetLastError() == hipSuccess ? PULSAR_OK : PULSAR_EHIP;
 }
 
 size_t scorer_split_lds_bytes(int64_t L, int num_blocks, int chunk, int vocab, int scorer) {
   return (size_t)split_score_layout(L, num_blocks, chunk, vocab, scorer).bytes;
+}
+
+bool scorer_split_pays(int batch, int64_t L, int num_blocks, int vocab, int scorer) {
+  return split_pays(scorer, batch, L, num_blocks, vocab);
 }
 
 int launch_scorer_split(const int32_t* ids, int batch, int64_t L, int num_blocks, int chunk,

@@ -20,6 +20,28 @@ __host__ __device__ inline int64_t split_seq_bytes(int num_blocks, int vocab) {
   return split_bits_bytes(num_blocks, vocab) + split_df_bytes(vocab);
 }
 
+// Whether the split path is the faster one for a batch that it takes, by
+// estimates in us that fit the times measured for both (1 to 16 sequences of
+// 4K to 128K ids, 4 to 16 blocks, vocabularies of 32000 and 128256) within
+// 20 %.  A workgroup that counts df over the whole sequence pays for its
+// blocks (a barrier and a round of table accesses each) and for its ids,
+// whatever the batch, and scores one block; the split path pays for three
+// launches, and per (sequence, block) for the vocabulary's tables.  The 3 us
+// are two more launches on the host.  Measured, one launch against split:
+//   Max-IDF, 1 x 8 x 2048 ids: 6.8 against 11.2 us; 1 x 16 x 8192: 20.8, 9.6
+//   BM25, 16 x 4 x 1024: 8.9, 16.3; 1 x 8 x 8192: 17.4, 14.8;
+//   16 x 16 x 8192: 29.5, 19.5
+inline bool split_pays(int scorer, int batch, int64_t L, int num_blocks, int vocab) {
+  const bool tf = scorer == PULSAR_SCORE_BM25 || scorer == PULSAR_SCORE_ENTROPY;
+  const bool maxidf = scorer == PULSAR_SCORE_MAXIDF;
+  const double kL = (double)L / 1024.0, grid = (double)batch * num_blocks;
+  const double one = maxidf ? 2.2 + 0.42 * num_blocks + 0.095 * kL
+                            : 5.0 + 0.30 * num_blocks + 0.11 * kL +
+                                  (tf ? 1.5 + 0.3 * kL / num_blocks : 0.0);
+  const double split = (maxidf ? 9.0 : tf ? 14.5 : 11.5) + (0.002 + 1.9e-7 * vocab) * grid;
+  return split + 3.0 < one;
+}
+
 // Copy of n 16-byte units (K rounds of kSplitThreads, n > (K - 1) *
 // kSplitThreads) from global memory into LDS: all K loads are issued before
 // the first store.  Lanes past the end copy the last unit onto itself, so no

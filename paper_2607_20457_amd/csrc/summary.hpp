@@ -121,6 +121,85 @@ __device__ __forceinline__ void stamp_pass_streaming(const int4* __restrict__ se
   __syncthreads();
 }
 
+// Stamp code of the kernels that keep their ids in registers, block j: the
+// high nibble of an id's byte holds df - 1 and the low nibble the stamp 15 - j
+// of the last block j it was seen in; kStampNever (0xFF) before it is first seen.  The minimum of a
+// chunk's codes then carries the chunk's minimum df - 1 in its high nibble,
+// so pass 2 needs no conversion of the table.  A lane whose id is not yet
+// stamped with j writes (df - 1 + 1, 15 - j); as with stamp_tokens, every
+// writer of one byte during one block writes the same value.  CHECK_NEVER:
+// kStampNever carries the stamp of block 0 in its low nibble, so a round that
+// may belong to block 0 also tests for it.  nd: each id's df - 1 once this
+// block is counted (final in the last block).
+template <bool CHECK_NEVER>
+__device__ __forceinline__ void rstamp_tokens(const int (&t)[4], int j, uint8_t* code,
+                                              uint32_t (&nd)[4]) {
+  uint32_t c[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) c[i] = code[t[i]];
+  const uint32_t sj = 15u - (uint32_t)j;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const bool stamped = (c[i] & 15u) == sj && (!CHECK_NEVER || c[i] != kStampNever);
+    const uint32_t nc = ((c[i] + 16u) & 0xF0u) | sj;  // 0xFF + 16 wraps to df - 1 = 0
+    nd[i] = (stamped ? c[i] : nc) >> 4;
+    if (!stamped) code[t[i]] = (uint8_t)nc;
+  }
+}
+
+// df of such a stamp code (0 for an id never seen)
+__device__ __forceinline__ uint32_t rstamp_df(uint32_t c) {
+  return c == kStampNever ? 0u : (c >> 4) + 1u;
+}
+
+// An id at or above vocab (the caller's error) reads and writes the last
+// entry of the table.  (As a function on unsigned values: min() of a vector's
+// element and an unsigned is taken for the signed overload.)
+__device__ __forceinline__ uint32_t clamp_id(uint32_t t, uint32_t vmax) {
+  return t < vmax ? t : vmax;
+}
+
+// A batch of fewer sequences than compute units takes several workgroups per
+// sequence (grid.y): each counts df over the whole sequence by itself and then
+// scores and selects the blocks of its part alone, so they share nothing.
+// BM25 of 48 x 8 x 8192 ids: 48.9 us with one workgroup per sequence, 22.2
+// with four; TF-IDF 20.2, 15.1; Max-IDF of 32 x 8 x 4096 ids 8.8, 7.9.
+// Blocks per part when the grid is to stay within the compute units.
+inline int blocks_per_part(int batch, int num_blocks) {
+  const int parts = batch >= 128 ? 1 : 256 / batch;
+  return (num_blocks + parts - 1) / parts;
+}
+
+// Slots: a sequence's ids in registers.  Slot r of a block is its ids
+// 4 (1024 r + tid) .. +3 in thread tid; a block of Lb ids has
+// ceil(Lb / SLOT_TOKENS) of them, the last one's lanes past the block idle.
+// Up to MAX_PLAIN_SLOTS slots are kept as loaded, more (MAX_SLOTS) packed.
+constexpr int SLOT_TOKENS = MAXIDF_THREADS * 4;
+constexpr int MAX_PLAIN_SLOTS = 16;
+constexpr int MAX_SLOTS = 32;
+
+// Block j and slot r within it, stepped along the slots without a division.
+struct SlotPos {
+  int j = 0, r = 0;
+  __device__ __forceinline__ void step(int slots_per_block) {
+    r = r + 1 == slots_per_block ? 0 : r + 1;
+    j += r == 0;
+  }
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t seq_resource(const int32_t* seq, int64_t L) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(seq), (short)0, (int)(L * 4),
+                                           kRawBuffer);
+}
+
+// This thread's ids of a slot; a slot that does not exist, and a lane past the
+// sequence, load nothing (zeros).
+__device__ __forceinline__ u32x4 load_slot(__amdgpu_buffer_rsrc_t rsrc, bool exists,
+                                           const SlotPos& p, int Lb, int64_t L, int tid) {
+  const int off = exists ? (p.j * Lb + p.r * SLOT_TOKENS) * 4 : (int)(L * 4);
+  return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, tid * 16, off, 0));
+}
+
 // x moved across lanes by a DPP control (quad permutes, row mirrors)
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_mov(uint32_t x) {
@@ -221,15 +300,15 @@ __device__ __forceinline__ void select_block(const KeyT* cv, int C, uint32_t key
 #undef SEL_KEY
 }
 
-// Top-k chunks of every block of sequence b from the chunk keys ([num_blocks]
+// Top-k chunks of blocks j0 .. j1 - 1 of sequence b from the chunk keys ([num_blocks]
 // [C] in LDS, every key <= key_hi); one wavefront per block.
 template <typename KeyT>
-__device__ __forceinline__ void select_topk(const KeyT* keys, int64_t b, int num_blocks, int C,
-                                            uint32_t key_hi, int topk,
+__device__ __forceinline__ void select_topk(const KeyT* keys, int64_t b, int num_blocks, int j0,
+                                            int j1, int C, uint32_t key_hi, int topk,
                                             int32_t* __restrict__ sel, int wave, int lane) {
   if (topk == 0) return;
   // the block loop is uniform across the wavefront: keep it scalar
-  for (int j = __builtin_amdgcn_readfirstlane(wave); j < num_blocks; j += MAXIDF_WAVES) {
+  for (int j = j0 + __builtin_amdgcn_readfirstlane(wave); j < j1; j += MAXIDF_WAVES) {
     const KeyT* cv = keys + (int64_t)j * C;
     int32_t* dst = sel + (b * num_blocks + j) * topk;
     if (C <= 4 * 64)

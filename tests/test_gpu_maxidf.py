@@ -275,3 +275,33 @@ def test_split_path_in_a_graph_replays():
             assert torch.equal(a.view(torch.int32), b.view(torch.int32)), f"replay {rep}"
         P.maxidf_summaries(other, N, m, k, V, return_mindf=True, workspace=ws)
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("b,L,N,m,V", [
+    (1, 4 * 4096, 4, 32, 128256),     # one whole slot per block
+    (3, 5 * 4100, 5, 4, 1000),        # a second slot of one lane; chunks of 4
+    (2, 16 * 4096, 16, 64, 131072),   # 16 slots kept as loaded
+    (1, 16 * 4096, 16, 32, 140000),   # the same above 17 bits
+    (2, 16 * 4112, 16, 16, 128256),   # 32 slots, packed
+    (1, 16 * 4112, 16, 16, 140000),   # streamed: too many slots for ids above 17 bits
+    (1, 11 * 8064, 11, 128, 40000),   # 22 packed slots, the second of a block not whole
+    (1, 3 * 12304, 3, 8, 5000),       # four slots per block
+    (2, 17 * 256, 17, 64, 300),       # more than 16 blocks: streamed, bitmaps
+    (100, 8 * 512, 8, 256, 700),      # two workgroups per sequence
+    (70, 5 * 96, 5, 32, 64),          # three, of two blocks and one
+    (300, 4 * 128, 4, 16, 500),       # more sequences than compute units
+])
+def test_slot_layouts(b, L, N, m, V):
+    # ids held in registers in slots of 4096, several workgroups per sequence
+    # for fewer than 128 sequences
+    ids = np.stack([workload.zipf_ids(7000 + L + i, L, V) for i in range(b)])
+    _check(ids, N, m, min(5, L // N // m), V)
+
+
+def test_slot_ids_outside_the_vocabulary_stay_in_the_table():
+    # the caller's error: an unspecified selection, no access outside
+    for V in (1000, 140000):
+        ids = torch.full((2, 4 * 4096), -1, dtype=torch.int32, device="cuda")
+        ids[1] = 2 ** 31 - 1
+        sel = P.maxidf_summaries(ids, 4, 32, 3, V, workspace=None)
+        assert sel.shape == (2, 4, 3) and int(sel.min()) >= 0 and int(sel.max()) < 128

@@ -151,3 +151,26 @@ def test_split_path_in_a_graph_replays():
             assert torch.equal(a.view(torch.int32), b.view(torch.int32)), f"replay {rep}"
         P.chunk_summaries(other, N, m, k, V, P.SCORE_ENTROPY, workspace=ws)
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("scorer", SCORERS)
+@pytest.mark.parametrize("b,L,N,m,V", [
+    (2, 8 * 4096, 8, 32, 20000),     # 8 slots of ids in registers
+    (1, 3 * 4100, 3, 4, 900),        # a second slot of one lane; chunks of 4
+    (1, 16 * 4096, 16, 64, 3000),    # 16 slots
+    (1, 16 * 4112, 16, 16, 3000),    # streamed
+    (100, 8 * 256, 8, 16, 500),      # two workgroups per sequence
+    (70, 5 * 96, 5, 32, 64),         # three, of two blocks and one
+    (130, 4 * 128, 4, 128, 90),      # one, chunks of a whole block
+])
+def test_slot_layouts(scorer, b, L, N, m, V):
+    ids = np.stack([workload.zipf_ids(8000 + L + i, L, V) for i in range(b)])
+    _check(ids, N, m, min(5, L // N // m), V, scorer)
+
+
+@pytest.mark.parametrize("scorer", SCORERS)
+@pytest.mark.parametrize("m", [4, 8, 64, 128, 256])
+def test_split_path_chunk_sizes(scorer, m):
+    # long enough that the workspace takes the split path
+    ids = workload.zipf_ids(8500 + m, 131072, 3000)[None]
+    _check(ids, 16, m, 7, 3000, scorer)
