@@ -259,11 +259,9 @@ int pulsar_phase1_attn(const void* Q, const void* K, const void* V, int batch, i
   const int64_t row_bytes = Lb * Hkv * d * 2;
   const int64_t src_off = (int64_t)block_idx * Lb * Hkv * d;
   const int64_t pitch = L * Hkv * d * 2;
-  st = launch_copy_rows(static_cast<const uint16_t*>(K) + src_off, pitch, K_keep, row_bytes,
-                        row_bytes, batch, (hipStream_t)stream);
-  if (st != PULSAR_OK) return st;
-  return launch_copy_rows(static_cast<const uint16_t*>(V) + src_off, pitch, V_keep, row_bytes,
-                          row_bytes, batch, (hipStream_t)stream);
+  return launch_keep_kv(static_cast<const uint16_t*>(K) + src_off,
+                        static_cast<const uint16_t*>(V) + src_off, pitch, K_keep, V_keep, row_bytes,
+                        batch, (hipStream_t)stream);
 }
 
 }  // extern "C"

@@ -242,5 +242,5 @@ int launch_gather_rope(const uint16_t* X, uint16_t* Y, int batch, int n, int64_t
 // IDF of a context with no tokens: every entry ln(num_blocks / 1).
 int launch_idf_fill(float* idf, int64_t n, int num_blocks, hipStream_t stream);
 
-int launch_copy_rows(const void* src, int64_t src_pitch, void* dst, int64_t dst_pitch,
-                     int64_t bytes_per_row, int rows, hipStream_t stream);
+int launch_keep_kv(const void* K, const void* V, int64_t src_pitch, void* K_out, void* V_out,
+                   int64_t bytes_per_row, int rows, hipStream_t stream);

@@ -32,28 +32,38 @@ int launch_positions(const RowMap& mp, const int32_t* sel, int64_t sel_bstride, 
 }
 
 // ---------------------------------------------------------------------------
-// Strided row copy (KV(B_i) retention, Appendix "KV Cache Discard").  Rows are
-// multiples of 16 bytes and 16-byte aligned (checked by the caller).
-__global__ __launch_bounds__(256) void copy_rows_kernel(const u32x4* __restrict__ src,
-                                                        int64_t src_pitch16,
-                                                        u32x4* __restrict__ dst,
-                                                        int64_t dst_pitch16, int64_t row16) {
+// KV(B_i) retention (Appendix "KV Cache Discard"): the same rows of K and V,
+// `rows` sequences of row16 16-byte words each, in one launch (grid.z).  Every
+// thread moves U words with all its loads in flight.  (K and V in a launch each,
+// a word per thread: 11 us for 2 x 8.4 MB, and a second launch on the host.)
+__global__ __launch_bounds__(256) void keep_kv_kernel(const u32x4* __restrict__ K,
+                                                      const u32x4* __restrict__ V,
+                                                      int64_t src_pitch16, u32x4* __restrict__ Ko,
+                                                      u32x4* __restrict__ Vo, int64_t row16) {
+  constexpr int U = 4;
   const int64_t row = blockIdx.y;
-  const u32x4* s = src + row * src_pitch16;
-  u32x4* d = dst + row * dst_pitch16;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < row16;
-       i += (int64_t)gridDim.x * 256)
-    d[i] = s[i];
+  const u32x4* s = (blockIdx.z ? V : K) + row * src_pitch16;
+  u32x4* d = (blockIdx.z ? Vo : Ko) + row * row16;
+  for (int64_t i0 = (int64_t)blockIdx.x * 256 * U + threadIdx.x; i0 < row16;
+       i0 += (int64_t)gridDim.x * 256 * U) {
+    u32x4 x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = s[min(i0 + u * 256, row16 - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * 256 < row16) d[i0 + u * 256] = x[u];
+  }
 }
 
-int launch_copy_rows(const void* src, int64_t src_pitch, void* dst, int64_t dst_pitch,
-                     int64_t bytes_per_row, int rows, hipStream_t stream) {
+int launch_keep_kv(const void* K, const void* V, int64_t src_pitch, void* K_out, void* V_out,
+                   int64_t bytes_per_row, int rows, hipStream_t stream) {
   if (rows == 0 || bytes_per_row == 0) return PULSAR_OK;
   const int64_t row16 = bytes_per_row / 16;
-  int64_t blocks = (row16 + 255) / 256;
+  int64_t blocks = (row16 + 1023) / 1024;
   if (blocks > 2048) blocks = 2048;
-  hipLaunchKernelGGL(copy_rows_kernel, dim3((unsigned)blocks, rows), dim3(256), 0, stream,
-                     (const u32x4*)src, src_pitch / 16, (u32x4*)dst, dst_pitch / 16, row16);
+  hipLaunchKernelGGL(keep_kv_kernel, dim3((unsigned)blocks, rows, 2), dim3(256), 0, stream,
+                     (const u32x4*)K, (const u32x4*)V, src_pitch / 16, (u32x4*)K_out, (u32x4*)V_out,
+                     row16);
   return hipGetLastError() == hipSuccess ? PULSAR_OK : PULSAR_EHIP;
 }
 
