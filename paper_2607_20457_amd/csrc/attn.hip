@@ -85,10 +85,26 @@ int launch_attention(const AttnLaunch& a, hipStream_t stream) {
   ka.nz = a.nz_kv * a.nsplit;
   ka.sched = nullptr;
   ka.grid = 0;
+  int n_cu = 256;
   if (a.causal && a.Hkv < kSchedWords) {
-    int n_cu = 0;
     ka.sched = sched_slot(stream, &n_cu);
     ka.grid = n_cu;
+  }
+  // The key-split form, where a launch has no more items than compute units:
+  // it then takes as long as its longest item, the last row tile over all
+  // keys, which the split halves (and its workgroups load every tile for half
+  // as many rows).  Without / with it, launch and copy: 20 items of 1280 rows,
+  // 4 / 1 heads of 64 34.3 / 24.5 us; 50 of 1580 rows, 8 / 2 heads of 128 45.2
+  // / 32.0; 172 of 5445 rows, 4 / 1 of 64 110 / 67; 240 of 3803 rows, 16 / 8 of
+  // 64 82 / 77.  With more items the queue balances them: 384 of 2851 rows, 16
+  // / 16 of 64 88 / 101, 424 of 3380 rows, 32 / 8 of 128 120 / 150.
+  const int64_t items = (int64_t)ka.n_row_tiles * ka.hsub * a.Hkv * ka.nz;
+  const int64_t split_lds = a.d == 128 ? attn_lds<128>(true, a.map.n_runs)
+                                       : attn_lds<64>(true, a.map.n_runs);
+  ka.ksplit = a.causal && items <= n_cu && a.n_kv >= 256 && split_lds + 16 <= PULSAR_LDS_BYTES;
+  if (ka.ksplit) {
+    ka.rows_per_wg /= 2;
+    ka.n_row_tiles = (a.n_q + ka.rows_per_wg - 1) / ka.rows_per_wg;
   }
   const bool lse = a.lse != nullptr;
   if (a.d == 128) return pulsar_attn::launch_d128(ka, a.causal != 0, lse, a.map.mode, stream);

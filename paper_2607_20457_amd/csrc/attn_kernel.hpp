@@ -20,6 +20,10 @@
 //   fixed share per XCD left the fast ones idle for the last few percent.
 //   Otherwise (Phase 2, or no counter slot) each workgroup is one item,
 //   with the KV head the fastest-varying index of its id.
+//   Key split (causal launches of few items): waves 4-7 take the rows of
+//   waves 0-3 and the odd key tiles, waves 0-3 the even ones, so that an item
+//   is half as many rows and half as long; each group stages its own tiles, and
+//   the two states are merged through LDS.
 //
 // Per wavefront, per 64-key tile, in two 32-key halves (32x32x16 bf16 MFMA,
 // fp32 accumulate)
@@ -68,6 +72,9 @@ struct KernelArgs {
   // and left zero by it), or null for one workgroup per item.
   unsigned* sched;
   int grid;           // workgroups of a persistent launch (one per CU)
+  // Key-split form (causal): the two wave groups of a workgroup take the same
+  // rows, half as many, and every second key tile each.
+  bool ksplit;
 };
 
 // Launch of one instantiation for head dimension D (defined in the per-D
@@ -102,6 +109,9 @@ struct Tile {
   static constexpr int STAGE = K_BYTES + V_BYTES;
   static constexpr int V_SEGS = V_BYTES / 1024;   // 1 KiB load segments of a V tile
   static constexpr int LDS = 3 * STAGE + 3 * BN * 4;  // three stages + three position rows
+  // key-split form: two K and two V slots and three position rows per wave group
+  static constexpr int GROUP = 2 * K_BYTES + 2 * V_BYTES;
+  static constexpr int LDS_SPLIT = 2 * GROUP + 6 * BN * 4;
 };
 
 
@@ -126,7 +136,7 @@ __device__ __forceinline__ int swap_bits23(int r) {
 // Matrix-phase fragment reads run this many matrix steps ahead.
 constexpr int MDEPTH = 4;
 
-template <int D, int QT, int WAVES, bool CAUSAL, bool LSE, int MODE>
+template <int D, int QT, int WAVES, bool CAUSAL, bool LSE, int MODE, bool KSPLIT>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(3 - QT, 3 - QT)))
 void attn_fwd_kernel(KernelArgs ka) {
   constexpr int THREADS = 64 * WAVES;
@@ -193,7 +203,9 @@ void attn_fwd_kernel(KernelArgs ka) {
 
   const int head = kvh * ka.group + hs * ka.heads_per_wg + (wave % ka.heads_per_wg);
   const int wg_row0 = row_tile * ka.rows_per_wg;
-  const int row0 = wg_row0 + (wave / ka.heads_per_wg) * QR;
+  const int grp = wave >> 2;
+  // waves of the workgroup's rows (KSPLIT: of one group), and this one's rows
+  const int row0 = wg_row0 + ((KSPLIT ? wave & 3 : wave) / ka.heads_per_wg) * QR;
 
   const int zkv = z / a.nsplit;
   const int split = z - zkv * a.nsplit;
@@ -201,7 +213,11 @@ void attn_fwd_kernel(KernelArgs ka) {
   int kv_end = min(a.n_kv, kv_begin + a.split_len);
   if (CAUSAL) kv_end = min(kv_end, wg_row0 + ka.rows_per_wg);
   const int n_keys = max(0, kv_end - kv_begin);
-  const int ntiles = (n_keys + BN - 1) / BN;
+  // tiles of the workgroup; KSPLIT: of each group, which takes every second
+  // one (group 1's last may lie past the keys: masked)
+  const int all_tiles = (n_keys + BN - 1) / BN;
+  const int ntiles = KSPLIT ? (all_tiles + 1) / 2 : all_tiles;
+  auto tile_key = [&](int t) { return kv_begin + (KSPLIT ? 2 * t + grp : t) * BN; };
 
   const int32_t* sel = a.sel ? a.sel + zkv * a.sel_bstride : nullptr;
   const int64_t q_row = (int64_t)a.Hq * D;
@@ -209,9 +225,12 @@ void attn_fwd_kernel(KernelArgs ka) {
   const float c2 = a.scale_log2;
 
   lds_u8* const stage0 = (lds_u8*)smem;  // LDS address space: reads take immediate offsets
-  int32_t* lpos = reinterpret_cast<int32_t*>(smem + 3 * T::STAGE);  // [3][BN]
+  // position rows [3][BN] (KSPLIT: of each group), then run_base[map.n_runs]
+  int32_t* const lpos_all =
+      reinterpret_cast<int32_t*>(smem + (KSPLIT ? 2 * T::GROUP : 3 * T::STAGE));
+  int32_t* const lpos = lpos_all + (KSPLIT ? grp * 3 * BN : 0);
   auto pos_of = [&](int t) { return lpos + (t % 3) * BN; };
-  int* run_base = lpos + 3 * BN;                                      // [map.n_runs]
+  int* const run_base = lpos_all + (KSPLIT ? 6 : 3) * BN;
   __syncthreads();  // the previous item's LDS reads are done
   if constexpr (MODE == MAP_SUMMARY)
     if (z != last_z) build_run_table(a.map, sel, run_base, tid, THREADS);
@@ -273,9 +292,9 @@ void attn_fwd_kernel(KernelArgs ka) {
   //   group of such a read touches in disjoint banks.  A key past the end
   //   reads row 0 of the sequence: finite, and its weight is zero.
   auto tile_positions = [&](int j, int32_t* dst) {
-    if (MODE != MAP_IDENTITY && tid < BN) {
-      const int k = kv_begin + j * BN + tid;
-      dst[tid] = k < kv_end ? row_position_m<MODE>(a.map, run_base, k) : -1;
+    if (MODE != MAP_IDENTITY && (KSPLIT ? (wave & 3) == 0 : tid < BN)) {
+      const int k = tile_key(j) + lane;
+      dst[lane] = k < kv_end ? row_position_m<MODE>(a.map, run_base, k) : -1;
     }
   };
   // The same in two steps for the loop, run by wave 0 inside its matrix
@@ -284,7 +303,7 @@ void attn_fwd_kernel(KernelArgs ka) {
   int2 pos_pending = int2{-1, -1};
   int pos_raw = 0;
   auto pos_start = [&](int j) {
-    const int k = kv_begin + j * BN + lane;
+    const int k = tile_key(j) + lane;
     pos_pending = k < kv_end ? row_position_split<MODE>(a.map, k) : int2{-1, -1};
     pos_raw = pos_pending.x >= 0 ? run_base[pos_pending.x] : 0;
   };
@@ -293,7 +312,7 @@ void attn_fwd_kernel(KernelArgs ka) {
   // the tile, or (identity map) directly; a key past the end reads row 0.
   auto kpos = [&](int t, int row) -> uint32_t {
     if constexpr (MODE == MAP_IDENTITY) {
-      const int k = kv_begin + t * BN + row;
+      const int k = tile_key(t) + row;
       return k < kv_end ? (uint32_t)(a.map.offset + k) : 0u;
     } else {
       return (uint32_t)max(pos_of(t)[row], 0);
@@ -301,10 +320,10 @@ void attn_fwd_kernel(KernelArgs ka) {
   };
   int dma_row[SEG_PER_WAVE];
   uint32_t dma_col[SEG_PER_WAVE];
-  const int wk = wave - 4;  // group-1 wave index
+  const int wk = wave & 3;  // wave within the group that moves K (V)
 #pragma unroll
   for (int i = 0; i < SEG_PER_WAVE; ++i) {
-    const int slot = (wk + 4 * i) * 64 + lane;
+    const int slot = (KSPLIT ? min(wk + 4 * i, T::K_CH - 1) : wk + 4 * i) * 64 + lane;
     const int r = slot / T::K_CH;
     const int col = slot - r * T::K_CH;
     dma_row[i] = swap_bits23(r & (BN - 1));
@@ -320,8 +339,10 @@ void attn_fwd_kernel(KernelArgs ka) {
     for (int i = 0; i < SEG_PER_WAVE; ++i) p[i] = kpos(tile, dma_row[i]);
 #pragma unroll
     for (int i = 0; i < SEG_PER_WAVE; ++i) {
-      const int sg = wk + 4 * i;
-      if (sg < T::K_CH)
+      // KSPLIT: every wave issues SEG_PER_WAVE loads, a segment past the last
+      // moves the last again, so that the waits can count them
+      const int sg = KSPLIT ? min(wk + 4 * i, T::K_CH - 1) : wk + 4 * i;
+      if (KSPLIT || sg < T::K_CH)
         lds_dma16(k_rsrc, __umul24(p[i], row_bytes) + dma_col[i], st_lds + sg * 1024);
     }
   };
@@ -331,20 +352,19 @@ void attn_fwd_kernel(KernelArgs ka) {
   uint32_t vdma_col[NVSEG];
 #pragma unroll
   for (int i = 0; i < NVSEG; ++i) {
-    const int slot = (wave + 4 * i) * 64 + lane;  // meaningful for group 0
+    const int slot = (wk + 4 * i) * 64 + lane;
     const int r = (slot / T::CPR) & (BN - 1);
     vdma_row[i] = r;
     vdma_col[i] = head_off + (uint32_t)((slot % T::CPR) ^ vswz(r)) * 16;
   }
   auto issue_v = [&](int tile, lds_u8* st) {
-    const uint32_t st_lds =
-        __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(st + T::K_BYTES));
+    const uint32_t st_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)st);
     uint32_t p[NVSEG];  // all positions first: each asm load orders later LDS reads
 #pragma unroll
     for (int i = 0; i < NVSEG; ++i) p[i] = kpos(tile, vdma_row[i]);
 #pragma unroll
     for (int i = 0; i < NVSEG; ++i)
-      lds_dma16(v_rsrc, __umul24(p[i], row_bytes) + vdma_col[i], st_lds + (wave + 4 * i) * 1024);
+      lds_dma16(v_rsrc, __umul24(p[i], row_bytes) + vdma_col[i], st_lds + (wk + 4 * i) * 1024);
   };
 
   // ---- building blocks of one 32-key half --------------------------------------
@@ -430,7 +450,9 @@ void attn_fwd_kernel(KernelArgs ka) {
       for (int t = 0; t < QT; ++t) acc[e][t] = f32x16{};
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
-      m_ref[t] = -INFINITY;
+      // (finite in the key-split form, where a row may see no key of group 1:
+      // its weights are then 0, not NaN)
+      m_ref[t] = KSPLIT ? -0x1p100f : -INFINITY;
       l_run[t] = 0.f;
 #pragma unroll
       for (int j = 0; j < NSUM; ++j) lr_run[t][j] = 0.f;
@@ -457,14 +479,24 @@ void attn_fwd_kernel(KernelArgs ka) {
   // either load was issued.  Wave 0 writes tile t's key positions during
   // V_{t-2}.
   static_assert(WAVES == 8, "the ping-pong schedule pairs waves w and w+4 on one SIMD");
-  const int grp = wave >> 2;
   // The stage offset goes through readfirstlane so that loop strength
   // reduction keeps it one scalar (fragment reads then take immediate
   // offsets from one base) instead of one induction variable per read.
-  auto stage_of = [&](int t) {
+  // KSPLIT: each group stages its own tiles, K_t in K slot t % 2 and V_t in V
+  // slot t % 2; its waves move both during V_{t-2} (K) and V_{t-1} (V) and wait
+  // for them one vector phase later.  K_{t-2} was last read in M_{t-2} and
+  // V_{t-2} in M_{t-1}, each before the load that replaces it.
+  lds_u8* const stage_g = stage0 + (KSPLIT ? grp * T::GROUP : 0);
+  auto k_slot = [&](int t) {
+    if (KSPLIT) return stage_g + __builtin_amdgcn_readfirstlane((t & 1) * T::K_BYTES);
     return stage0 + __builtin_amdgcn_readfirstlane((t % 3) * T::STAGE);
   };
-  auto key_of = [&](int t, int u) { return kv_begin + t * BN + 32 * u; };
+  auto v_slot = [&](int t) {  // t >= -1
+    if (KSPLIT)
+      return stage_g + __builtin_amdgcn_readfirstlane(2 * T::K_BYTES + (t & 1) * T::V_BYTES);
+    return stage0 + __builtin_amdgcn_readfirstlane(((t + 3) % 3) * T::STAGE + T::K_BYTES);
+  };
+  auto key_of = [&](int t, int u) { return tile_key(t) + 32 * u; };
   auto edge = [&](int t, int u) {
     const int kh = key_of(t, u);
     return CAUSAL ? (kh + 31 > row0) : (kh + 32 > kv_end);
@@ -489,7 +521,8 @@ void attn_fwd_kernel(KernelArgs ka) {
 #pragma unroll
     for (int i = 0; i < MDEPTH; ++i) ring[i] = frag(i);
     // wave 0 forms the key positions of tile pos_tile (if any) here
-    const bool do_pos = MODE != MAP_IDENTITY && wave == 0 && pos_tile >= 0;
+    const bool do_pos =
+        MODE != MAP_IDENTITY && (KSPLIT ? wk == 0 : wave == 0) && pos_tile >= 0;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       if (i == 2 && do_pos) pos_start(pos_tile);
@@ -525,21 +558,21 @@ void attn_fwd_kernel(KernelArgs ka) {
       for (int c = 0; c < 2; ++c)
 #pragma unroll
         for (int t = 0; t < QT; ++t) P[u][c][t] = bf16x8{};
-    for (int i = tid; i < T::V_BYTES / 16; i += THREADS)
-      reinterpret_cast<__attribute__((address_space(3))) u32x4*>(stage_of(2) + T::K_BYTES)[i] =
+    // V of "tile -1", which M_0 multiplies by P = 0
+    for (int i = KSPLIT ? tid & 255 : tid; i < T::V_BYTES / 16; i += KSPLIT ? 256 : THREADS)
+      reinterpret_cast<__attribute__((address_space(3))) u32x4*>(v_slot(-1))[i] =
           u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
     if (ntiles > 0) {
-      if (grp == 1) issue_k(0, stage_of(0));
-      if (grp == 0) issue_v(0, stage_of(0));
+      if (KSPLIT || grp == 1) issue_k(0, k_slot(0));
+      if (KSPLIT || grp == 0) issue_v(0, v_slot(0));
     }
     if (ntiles > 1) tile_positions(1, pos_of(1));
-    if (grp == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (KSPLIT) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NVSEG) : "memory");
+    else if (grp == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (grp == 1) {  // K of tile 1, then group 1's lag barrier
-      if (ntiles > 1) issue_k(1, stage_of(1));
-      __syncthreads();
-    }
+    if ((KSPLIT || grp == 1) && ntiles > 1) issue_k(1, k_slot(1));
+    if (grp == 1) __syncthreads();  // group 1's lag barrier
     // The matrix phase runs at raised wave priority, so that the SIMD's
     // arbiter issues its matrix instructions ahead of the partner wave's
     // vector instructions whenever both are ready.
@@ -558,14 +591,14 @@ void attn_fwd_kernel(KernelArgs ka) {
     auto m_phase_end = [&]() {
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_setprio(0);
-      if (grp == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (!KSPLIT && grp == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       phase_barrier();
     };
     // V_m: weights of tile m (both halves; a half with no visible key is
     // fully masked and weighs zero).
     auto v_phase = [&](int m) {
-      if (grp == 1 && m + 2 < ntiles) issue_k(m + 2, stage_of(m + 2));
-      if (grp == 0 && m + 1 < ntiles) issue_v(m + 1, stage_of(m + 1));
+      if ((KSPLIT || grp == 1) && m + 2 < ntiles) issue_k(m + 2, k_slot(m + 2));
+      if ((KSPLIT || grp == 0) && m + 1 < ntiles) issue_v(m + 1, v_slot(m + 1));
 #pragma unroll
       for (int u = 0; u < 2; ++u)
         if (EXACT || edge(m, u)) apply_mask(key_of(m, u), S[u]);
@@ -589,13 +622,24 @@ void attn_fwd_kernel(KernelArgs ka) {
         }
       } else if (m == 0) {  // half 0 of tile 0 always has a visible key
 #pragma unroll
-        for (int t = 0; t < QT; ++t) m_ref[t] = row_max(S[0][t]);
+        for (int t = 0; t < QT; ++t) {
+          m_ref[t] = row_max(S[0][t]);
+          // (KSPLIT: nor does a row that sees no key of group 1's first tile
+          // see one of its later tiles; any reference gives them weight 0)
+          if (KSPLIT && key_of(0, 0) > min(row0 + t * 32 + l32, kv_end - 1)) m_ref[t] = 0.f;
+        }
       }
       weights(S[0], P[0]);
       weights(S[1], P[1]);
       // V of tile m must be in LDS for M_{m+1}; only V of tile m+1 may still
       // be in flight.
-      if (grp == 0) {
+      // (KSPLIT: and K of tile m + 1, of the loads of the last vector phase)
+      if (KSPLIT) {
+        if (m + 2 < ntiles)
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NVSEG + SEG_PER_WAVE) : "memory");
+        else if (m + 1 < ntiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NVSEG) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      } else if (grp == 0) {
         if (m + 1 < ntiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NVSEG) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       }
@@ -610,7 +654,7 @@ void attn_fwd_kernel(KernelArgs ka) {
       // K issue in its V_m and group 0's V issue in V_{m+1}); the row it
       // overwrites last served tile m - 1, whose last reader ran two
       // intervals earlier
-      m_phase_full(stage_of(m + 2) + T::K_BYTES, stage_of(m), m + 2 < ntiles ? m + 2 : -1);
+      m_phase_full(v_slot(m - 1), k_slot(m), m + 2 < ntiles ? m + 2 : -1);
       m_phase_end();
       if (m < ntiles) v_phase(m);
     }
@@ -634,6 +678,61 @@ void attn_fwd_kernel(KernelArgs ka) {
   // which workgroup frees up first, which spreads the end of the launch.
   if (persistent && tid == 0) next_item = claim();
 
+  if constexpr (KSPLIT) {
+    // Group 1 hands its state to group 0 (the same rows, the other tiles)
+    // through the stages, which everyone is done with (the overflow vote).
+    float* const st = reinterpret_cast<float*>(smem) + wk * (QT * (DT * 16 + 3) * 64);
+    if (grp == 1) {
+#pragma unroll
+      for (int t = 0; t < QT; ++t) {
+        const float lr = (lr_run[t][0] + lr_run[t][1]) + (lr_run[t][2] + lr_run[t][3]);
+        float* const sum = st + QT * DT * 16 * 64 + t * 3 * 64 + lane;
+        sum[0] = m_ref[t];
+        sum[64] = l_run[t];
+        sum[128] = lr;
+#pragma unroll
+        for (int e = 0; e < DT; ++e)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4)
+            *reinterpret_cast<f32x4*>(st + (((t * DT + e) * 4 + q4) * 64 + lane) * 4) =
+                f32x4{acc[e][t][4 * q4], acc[e][t][4 * q4 + 1], acc[e][t][4 * q4 + 2],
+                      acc[e][t][4 * q4 + 3]};
+      }
+    }
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+      for (int t = 0; t < QT; ++t) {
+        const float* const sum = st + QT * DT * 16 * 64 + t * 3 * 64 + lane;
+        const float m1 = sum[0], l1 = sum[64], lr1 = sum[128];
+        // a group without a visible key of the row has sum 0; its reference
+        // must not hide the other's
+        const bool has0 = lr_run[t][0] + lr_run[t][1] + lr_run[t][2] + lr_run[t][3] +
+                              __shfl_xor(lr_run[t][0] + lr_run[t][1] + lr_run[t][2] + lr_run[t][3],
+                                         32, 64) > 0.f;
+        const bool has1 = lr1 + __shfl_xor(lr1, 32, 64) > 0.f;
+        const float m = has0 && has1 ? fmaxf(m_ref[t], m1) : has1 ? m1 : m_ref[t];
+        const float w0 = has0 ? __builtin_amdgcn_exp2f(m_ref[t] - m) : 0.f;
+        const float w1 = has1 ? __builtin_amdgcn_exp2f(m1 - m) : 0.f;
+        l_run[t] = l_run[t] * w0 + l1 * w1;
+#pragma unroll
+        for (int j = 0; j < NSUM; ++j) lr_run[t][j] *= w0;
+        lr_run[t][0] += lr1 * w1;
+        m_ref[t] = m;
+#pragma unroll
+        for (int e = 0; e < DT; ++e)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const f32x4 o = *reinterpret_cast<const f32x4*>(
+                st + (((t * DT + e) * 4 + q4) * 64 + lane) * 4);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              acc[e][t][4 * q4 + i] = acc[e][t][4 * q4 + i] * w0 + o[i] * w1;
+          }
+      }
+    }
+  }
+
   // ---- epilogue: normalise, write O and LSE ---------------------------------
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
@@ -642,7 +741,7 @@ void attn_fwd_kernel(KernelArgs ka) {
     const float lr_tot = lr + __shfl_xor(lr, 32, 64);
     const float inv = lr_tot > 0.f ? 1.f / lr_tot : 0.f;
     const int qrow = row0 + t * 32 + l32;
-    if (qrow < a.n_q) {
+    if (qrow < a.n_q && (!KSPLIT || grp == 0)) {
       const int64_t obase = ((int64_t)z * a.o_zstride) + ((int64_t)qrow * a.Hq + head) * D;
 #pragma unroll
       for (int e = 0; e < DT; ++e)
@@ -679,16 +778,22 @@ void attn_fwd_kernel(KernelArgs ka) {
   }
 }
 
-template <int D, int QT, int WAVES, bool CAUSAL, bool LSE, int MODE>
+// Dynamic LDS of a launch.
+template <int D>
+int64_t attn_lds(bool ksplit, int n_runs) {
+  return (ksplit ? Tile<D>::LDS_SPLIT : Tile<D>::LDS) + (int64_t)n_runs * 4;
+}
+
+template <int D, int QT, int WAVES, bool CAUSAL, bool LSE, int MODE, bool KSPLIT>
 int launch_impl(const KernelArgs& ka, hipStream_t stream) {
   int64_t nwg = (int64_t)ka.n_row_tiles * ka.hsub * ka.a.Hkv * ka.nz;
   if (nwg == 0) return PULSAR_OK;
   if (CAUSAL && ka.sched != nullptr && nwg > ka.grid) nwg = ka.grid;
   if (nwg > 0x7fffffff) return PULSAR_EUNSUPPORTED;
-  const int64_t lds = Tile<D>::LDS + (int64_t)ka.a.map.n_runs * 4;
+  const int64_t lds = attn_lds<D>(KSPLIT, ka.a.map.n_runs);
   // the kernel's static LDS (the item broadcast) comes on top, aligned
   if (lds + 16 > PULSAR_LDS_BYTES) return PULSAR_EUNSUPPORTED;
-  auto kern = attn_fwd_kernel<D, QT, WAVES, CAUSAL, LSE, MODE>;
+  auto kern = attn_fwd_kernel<D, QT, WAVES, CAUSAL, LSE, MODE, KSPLIT>;
   if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)lds) != hipSuccess)
     return PULSAR_EHIP;
@@ -698,27 +803,28 @@ int launch_impl(const KernelArgs& ka, hipStream_t stream) {
 
 
 // Every (causal, lse, map mode) instantiation for head dimension D: the
-// unmasked (Phase 2) kernels only see the identity map.
+// unmasked (Phase 2) kernels only see the identity map, the causal ones come
+// with and without the key split.
+template <int D, int QT, int WAVES_C, int MODE>
+int launch_causal(const KernelArgs& ka, bool lse, hipStream_t stream) {
+  if (ka.ksplit)
+    return lse ? launch_impl<D, QT, WAVES_C, true, true, MODE, true>(ka, stream)
+               : launch_impl<D, QT, WAVES_C, true, false, MODE, true>(ka, stream);
+  return lse ? launch_impl<D, QT, WAVES_C, true, true, MODE, false>(ka, stream)
+             : launch_impl<D, QT, WAVES_C, true, false, MODE, false>(ka, stream);
+}
 template <int D, int QT, int WAVES_C, int WAVES_P>
 int launch_for_d(const KernelArgs& ka, bool causal, bool lse, int mode, hipStream_t stream) {
   if (!causal) {
     if (mode != MAP_IDENTITY) return PULSAR_EUNSUPPORTED;
-    return lse ? launch_impl<D, QT, WAVES_P, false, true, MAP_IDENTITY>(ka, stream)
-               : launch_impl<D, QT, WAVES_P, false, false, MAP_IDENTITY>(ka, stream);
+    return lse ? launch_impl<D, QT, WAVES_P, false, true, MAP_IDENTITY, false>(ka, stream)
+               : launch_impl<D, QT, WAVES_P, false, false, MAP_IDENTITY, false>(ka, stream);
   }
   switch (mode) {
-    case MAP_IDENTITY:
-      return lse ? launch_impl<D, QT, WAVES_C, true, true, MAP_IDENTITY>(ka, stream)
-                 : launch_impl<D, QT, WAVES_C, true, false, MAP_IDENTITY>(ka, stream);
-    case MAP_SUMMARY:
-      return lse ? launch_impl<D, QT, WAVES_C, true, true, MAP_SUMMARY>(ka, stream)
-                 : launch_impl<D, QT, WAVES_C, true, false, MAP_SUMMARY>(ka, stream);
-    case MAP_ANCHOR:
-      return lse ? launch_impl<D, QT, WAVES_C, true, true, MAP_ANCHOR>(ka, stream)
-                 : launch_impl<D, QT, WAVES_C, true, false, MAP_ANCHOR>(ka, stream);
-    case MAP_EVEN:
-      return lse ? launch_impl<D, QT, WAVES_C, true, true, MAP_EVEN>(ka, stream)
-                 : launch_impl<D, QT, WAVES_C, true, false, MAP_EVEN>(ka, stream);
+    case MAP_IDENTITY: return launch_causal<D, QT, WAVES_C, MAP_IDENTITY>(ka, lse, stream);
+    case MAP_SUMMARY: return launch_causal<D, QT, WAVES_C, MAP_SUMMARY>(ka, lse, stream);
+    case MAP_ANCHOR: return launch_causal<D, QT, WAVES_C, MAP_ANCHOR>(ka, lse, stream);
+    case MAP_EVEN: return launch_causal<D, QT, WAVES_C, MAP_EVEN>(ka, lse, stream);
     default: return PULSAR_EINVAL;
   }
 }

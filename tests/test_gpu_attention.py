@@ -408,3 +408,39 @@ def test_sweep_batch4_anchor_bf16_no_lse():
                                  f"sweep anchor b={b} block {i}")
         del O
     _SWEEP.clear()
+
+
+@pytest.mark.parametrize("Lb,N,sink,m,k,Hq,Hkv,d", [
+    (256, 2, 0, 16, 2, 4, 1, 64),       # 256 and 288 rows: whole tiles, an odd number
+    (257, 2, 1, 1, 1, 4, 4, 64),        # one row past a tile, 128 rows per workgroup
+    (320, 3, 3, 20, 5, 8, 4, 64),       # two heads per KV head, ragged prefix
+    (383, 2, 50, 20, 7, 8, 2, 128),     # last tile of one group past the keys
+    (449, 2, 64, 32, 3, 16, 2, 128),    # 8 heads per KV head
+])
+@pytest.mark.parametrize("mode", [P.PREFIX_SUMMARY, P.PREFIX_ANCHOR, P.PREFIX_EVEN])
+def test_key_split_shapes_full(Lb, N, sink, m, k, Hq, Hkv, d, mode):
+    # few row tiles: the wave groups of a workgroup take every second key tile
+    cfg = workload.Config("split", L=Lb * N, vocab=100, num_blocks=N, sink=sink, chunk=m, topk=k,
+                          Hq=Hq, Hkv=Hkv, d=d)
+    q, kk, v = (workload.bf16_normal(9000 + Lb + s, (2, cfg.L, h, d))
+                for s, h in ((0, Hq), (1, Hkv), (2, Hkv)))
+    rng = np.random.default_rng(Lb)
+    sel = np.sort(np.stack([[rng.choice(Lb // m, k, replace=False) for _ in range(N)]
+                            for _ in range(2)]), axis=2).astype(np.int32)
+    for i in (0, N - 1):
+        for b in (0, 1):
+            _full_check(cfg, i, mode, sel if mode == P.PREFIX_SUMMARY else None, q, kk, v, b)
+
+
+@pytest.mark.parametrize("key", [70, 200, 400])
+def test_key_split_far_larger_later_score(key):
+    # a key of either group's later tiles far above every row's first scores:
+    # the exact pass, for rows that see no key of group 1 as well
+    cfg = workload.Config("spike", L=512, vocab=100, num_blocks=1, sink=0, chunk=16, topk=0, Hq=4,
+                          Hkv=1, d=64)
+    q = workload.bf16_bits_to_f32(workload.bf16_normal(9101, (1, 512, 4, 64))) + 1.0
+    k = workload.bf16_bits_to_f32(workload.bf16_normal(9102, (1, 512, 1, 64)))
+    k[0, key] = 16.0
+    v = workload.bf16_normal(9103, (1, 512, 1, 64))
+    _full_check(cfg, 0, P.PREFIX_SUMMARY, None, workload.f32_to_bf16_bits(q),
+                workload.f32_to_bf16_bits(k), v)
