@@ -248,25 +248,7 @@ void attn_fwd_kernel(KernelArgs ka) {
       kBufferFlags);
   const uint32_t head_off = (uint32_t)(kvh * D * 2);
 
-  // ---- Q fragments (B operand of S^T = K Q^T) --------------------------------
-  bf16x8 qf[QT][DS];
-#pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    const int r = row0 + t * 32 + l32;
-    const int p = r < a.n_q ? row_position_m<MODE>(a.map, run_base, r) : 0;
-    const bf16x8* src = reinterpret_cast<const bf16x8*>(Qz + (int64_t)p * q_row) + g;
-#pragma unroll
-    for (int s = 0; s < DS; ++s) qf[t][s] = r < a.n_q ? src[2 * s] : bf16x8{};
-  }
-  // Wait for the Q loads here: passing each fragment through an empty asm
-  // statement makes the compiler wait for it before the loop and treat it as
-  // defined afterwards, so no wait inside the key loop is tied to the Q loads
-  // (which would also wait for the next tile's prefetch issued after them).
-#pragma unroll
-  for (int t = 0; t < QT; ++t)
-#pragma unroll
-    for (int s = 0; s < DS; ++s) asm volatile("" : "+v"(qf[t][s]));
-
+  bf16x8 qf[QT][DS];  // Q fragments (B operand of S^T = K Q^T)
   f32x16 acc[DT][QT];
   // reference max, fp32 weight sum, and the bf16 weight sum in NSUM
   // independent partial sums (so the dot2 accumulations are not one chain)
@@ -544,20 +526,11 @@ void attn_fwd_kernel(KernelArgs ka) {
     }
   };
 
-  // EXACT = false: fixed per-row reference (the row's maximum over the
-  // first 32 keys), O touched only by MFMA.  EXACT = true: classic online
-  // softmax; the running maximum is raised when a tile's maximum exceeds it
-  // by more than 2^8, and O and the sums are rescaled.
-  auto run_pass = [&](auto exact_tag) {
-    constexpr bool EXACT = decltype(exact_tag)::value;
-    reset();
+  // Start of a pass: the positions of tiles 0 and 1, and K and V of tile 0 on
+  // their way.
+  auto begin_pass = [&]() {
     tile_positions(0, pos_of(0));
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int t = 0; t < QT; ++t) P[u][c][t] = bf16x8{};
+    if (ntiles > 1) tile_positions(1, pos_of(1));
     // V of "tile -1", which M_0 multiplies by P = 0
     for (int i = KSPLIT ? tid & 255 : tid; i < T::V_BYTES / 16; i += KSPLIT ? 256 : THREADS)
       reinterpret_cast<__attribute__((address_space(3))) u32x4*>(v_slot(-1))[i] =
@@ -567,7 +540,22 @@ void attn_fwd_kernel(KernelArgs ka) {
       if (KSPLIT || grp == 1) issue_k(0, k_slot(0));
       if (KSPLIT || grp == 0) issue_v(0, v_slot(0));
     }
-    if (ntiles > 1) tile_positions(1, pos_of(1));
+  };
+
+  // EXACT = false: fixed per-row reference (the row's maximum over the
+  // first 32 keys), O touched only by MFMA.  EXACT = true: classic online
+  // softmax; the running maximum is raised when a tile's maximum exceeds it
+  // by more than 2^8, and O and the sums are rescaled.
+  auto run_pass = [&](auto exact_tag) {
+    constexpr bool EXACT = decltype(exact_tag)::value;
+    reset();
+    if (EXACT) begin_pass();
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int t = 0; t < QT; ++t) P[u][c][t] = bf16x8{};
     if (KSPLIT) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NVSEG) : "memory");
     else if (grp == 1) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -660,6 +648,25 @@ void attn_fwd_kernel(KernelArgs ka) {
     }
     if (grp == 0) __syncthreads();  // matches group 1's lag barrier
   };
+
+  // The first tile is on its way while Q is loaded.
+  begin_pass();
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    const int r = row0 + t * 32 + l32;
+    const int p = r < a.n_q ? row_position_m<MODE>(a.map, run_base, r) : 0;
+    const bf16x8* src = reinterpret_cast<const bf16x8*>(Qz + (int64_t)p * q_row) + g;
+#pragma unroll
+    for (int s = 0; s < DS; ++s) qf[t][s] = r < a.n_q ? src[2 * s] : bf16x8{};
+  }
+  // Wait for the Q loads here: passing each fragment through an empty asm
+  // statement makes the compiler wait for it before the loop and treat it as
+  // defined afterwards, so no wait inside the key loop is tied to the Q loads
+  // (which would also wait for the next tile's prefetch issued after them).
+#pragma unroll
+  for (int t = 0; t < QT; ++t)
+#pragma unroll
+    for (int s = 0; s < DS; ++s) asm volatile("" : "+v"(qf[t][s]));
 
   // ---- fast pass, then the exact pass only after an overflow flag -----------
   run_pass(std::false_type{});
