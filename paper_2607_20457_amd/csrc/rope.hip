@@ -40,13 +40,14 @@ constexpr double kInvTwoPi = 0.15915494309189535;
 // One row of H heads: 16-byte loads of src (already offset by this lane's
 // 8 pairs), rotation by the angles of position p + p_add (ROTATE) or a plain
 // copy, 16-byte stores to dst.  `w_pair` and `p` may still be loading: the
-// first data is requested before they are used.
-template <int D, bool ROTATE>
+// first data is requested before they are used.  U: steps of heads whose loads
+// are in flight together (no more than the row has).  NT: the data passes the
+// caches by.
+template <int D, bool ROTATE, int U, bool NT>
 __device__ __forceinline__ void rope_row(const uint16_t* src, uint16_t* dst, int H, int64_t p,
                                          int64_t p_add, double w_pair, int lane) {
   constexpr int G = D / 16;     // lanes per head: pairs 8j .. 8j+7 each
   constexpr int HPW = 64 / G;   // heads per wavefront step
-  constexpr int U = 4;          // steps whose loads are in flight together
   const int j = lane % G, hl = lane / G;
   // Heads hl, hl + HPW, ...: one step covers HPW heads of the row, its low
   // and high halves as two runs of contiguous 16-byte chunks.  Loads are
@@ -56,8 +57,10 @@ __device__ __forceinline__ void rope_row(const uint16_t* src, uint16_t* dst, int
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int hh = min(h0 + u * HPW + hl, H - 1);
-      lo[u] = *reinterpret_cast<const u32x4*>(src + (int64_t)hh * D);
-      hi[u] = *reinterpret_cast<const u32x4*>(src + (int64_t)hh * D + D / 2);
+      const u32x4* const p_lo = reinterpret_cast<const u32x4*>(src + (int64_t)hh * D);
+      const u32x4* const p_hi = reinterpret_cast<const u32x4*>(src + (int64_t)hh * D + D / 2);
+      lo[u] = NT ? __builtin_nontemporal_load(p_lo) : *p_lo;
+      hi[u] = NT ? __builtin_nontemporal_load(p_hi) : *p_hi;
     }
   };
   // The row's angles: lane (hl, j) forms that of pair 8j + hl % 8, then
@@ -111,14 +114,21 @@ __device__ __forceinline__ void rope_row(const uint16_t* src, uint16_t* dst, int
       if (hh < H) {
         u32x4 olo = clo[u], ohi = chi[u];
         if constexpr (ROTATE) rotate(clo[u], chi[u], olo, ohi);
-        *reinterpret_cast<u32x4*>(dst + (int64_t)hh * D) = olo;
-        *reinterpret_cast<u32x4*>(dst + (int64_t)hh * D + D / 2) = ohi;
+        u32x4* const d_lo = reinterpret_cast<u32x4*>(dst + (int64_t)hh * D);
+        u32x4* const d_hi = reinterpret_cast<u32x4*>(dst + (int64_t)hh * D + D / 2);
+        if constexpr (NT) {
+          __builtin_nontemporal_store(olo, d_lo);
+          __builtin_nontemporal_store(ohi, d_hi);
+        } else {
+          *d_lo = olo;
+          *d_hi = ohi;
+        }
       }
     }
   }
 }
 
-template <int D, bool HAS_POS>
+template <int D, bool HAS_POS, int U, bool NT>
 __global__ __launch_bounds__(kRopeThreads) void rope_kernel(uint16_t* __restrict__ X,
                                                             int64_t rows, int64_t n_rows, int H,
                                                             const int32_t* __restrict__ pos,
@@ -132,7 +142,7 @@ __global__ __launch_bounds__(kRopeThreads) void rope_kernel(uint16_t* __restrict
   // The frequency and the position are requested before the first data.
   const double w = f.w[8 * j + (hl & 7)];
   const int64_t p = HAS_POS ? (int64_t)pos[row] : row % n_rows;
-  rope_row<D, true>(base, base, H, p, pos_offset, w, lane);
+  rope_row<D, true, U, NT>(base, base, H, p, pos_offset, w, lane);
 }
 
 // Rows of block i's assembled Phase-1 input (Eq. 3), gathered from the
@@ -170,7 +180,23 @@ __global__ __launch_bounds__(kRopeThreads) void gather_rope_kernel(
   const uint16_t* src = X + b * x_bstride + (int64_t)p * H * D + 8 * j;
   uint16_t* dst = Y + row * (int64_t)H * D + 8 * j;
   const double w = f.w[8 * j + (hl & 7)];
-  rope_row<D, ROT != 0>(src, dst, H, ROT == 2 ? (int64_t)r : (int64_t)p, 0, w, lane);
+  rope_row<D, ROT != 0, 4, false>(src, dst, H, ROT == 2 ? (int64_t)r : (int64_t)p, 0, w, lane);
+}
+
+typedef void (*RopeKernel)(uint16_t*, int64_t, int64_t, int, const int32_t*, int64_t, RopeFreqs);
+// Steps in flight: as many as the row has, up to four (a row of one step loaded
+// its last heads three times more: 8192 rows of 8 heads of 128 7.2 -> 5.9 us).
+template <int D, bool HAS_POS, bool NT>
+RopeKernel rope_for_heads(int H) {
+  const int steps = (H + 1024 / D - 1) / (1024 / D);  // of 64 / (D / 16) heads
+  return steps <= 1   ? rope_kernel<D, HAS_POS, 1, NT>
+         : steps <= 2 ? rope_kernel<D, HAS_POS, 2, NT>
+                      : rope_kernel<D, HAS_POS, 4, NT>;
+}
+template <int D>
+RopeKernel rope_for(int H, bool has_pos, bool nt) {
+  return has_pos ? (nt ? rope_for_heads<D, true, true>(H) : rope_for_heads<D, true, false>(H))
+                 : (nt ? rope_for_heads<D, false, true>(H) : rope_for_heads<D, false, false>(H));
 }
 
 // The table w_i: the caller's (checked finite) or base^(-2i/d).
@@ -230,8 +256,14 @@ int pulsar_rope(void* X, int batch, int64_t n_rows, int H, int d, const int32_t*
   const int64_t blocks = (rows + kRopeThreads / 64 - 1) / (kRopeThreads / 64);  // a wave per row
   if (blocks > 0x7fffffff) return PULSAR_EUNSUPPORTED;
   auto s = (hipStream_t)stream;
-  const auto kern = d == 128 ? (pos ? rope_kernel<128, true> : rope_kernel<128, false>)
-                             : (pos ? rope_kernel<64, true> : rope_kernel<64, false>);
+  // Nontemporal accesses from 64 MB on.  A pass over data that comes from HBM
+  // is 10 to 12 % faster with them (256 MB 94.8 -> 86.1 us, 6.2 TB/s; 64 MB 25.8
+  // -> 22.7), one over data that the 256 MB last-level cache still holds is
+  // slower (64 MB 20.6 -> 22.0 us, 32 MB 8.4 -> 11.1): tensors of that size are
+  // mostly gone from it by the time a layer's rotation reads them.
+  const bool nt = rows * H * d * 2 >= (int64_t)64 << 20;
+  const RopeKernel kern = d == 128 ? rope_for<128>(H, pos != nullptr, nt)
+                                   : rope_for<64>(H, pos != nullptr, nt);
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kRopeThreads), 0, s, (uint16_t*)X, rows,
                      n_rows, H, pos, pos_offset, f);
   return hipGetLastError() == hipSuccess ? PULSAR_OK : PULSAR_EHIP;

@@ -239,3 +239,25 @@ def test_contiguous_phase1_and_phase2_positions_end_to_end():
     torch.cuda.synchronize()
     ref = orope.rope(f64(xq), qpos, w)
     check_rounding(_bits(Xq), ref, f64(xq), "contiguous Phase-2 queries")
+
+
+@pytest.mark.parametrize("H,d", [(8, 128), (9, 128), (33, 128), (16, 64), (20, 64), (65, 64)])
+@pytest.mark.parametrize("posmode", ["rows", "array"])
+def test_rope_of_large_tensors_equals_its_halves(H, d, posmode):
+    # from 64 MB on the data passes the caches by; one, two and four steps of
+    # heads in flight, and more heads than that.  The halves are below the
+    # line, and below it the other tests compare with the oracle.
+    n = ((64 << 20) // (H * d * 2) + 2) // 2 * 2
+    X = torch.randn((1, n, H, d), generator=torch.Generator("cuda").manual_seed(H), device="cuda",
+                    dtype=torch.bfloat16)
+    pos = None if posmode == "rows" else \
+        torch.randint(0, 140000, (1, n), dtype=torch.int32, device="cuda")
+    parts = [X[:, :n // 2].clone(), X[:, n // 2:].clone()]
+    assert X.numel() * 2 >= 64 << 20 > parts[0].numel() * 2
+    P.rope_(X, pos)
+    for i, part in enumerate(parts):
+        if pos is None:
+            P.rope_(part, pos_offset=i * (n // 2))
+        else:
+            P.rope_(part, pos[:, i * (n // 2):(i + 1) * (n // 2)].contiguous())
+    assert torch.equal(X, torch.cat(parts, 1))
