@@ -301,7 +301,8 @@ int pulsar_phase1_attn(const void* Q, const void* K, const void* V, int batch, i
 
 /*
  * Device workspace, in bytes, that pulsar_phase2_partial needs for these
- * shapes (0 when none is needed).  Host-only.
+ * shapes, and for fewer tokens over no more and no longer shards (0 when these
+ * shapes need none).  Host-only.
  */
 size_t pulsar_phase2_workspace_bytes(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d);
 
@@ -319,8 +320,9 @@ size_t pulsar_phase2_workspace_bytes(int n_shards, int Tq, int64_t S, int Hq, in
  * o_parts     out float32 [n_shards, Tq, Hq, d].
  * lse_parts   out float32 [n_shards, Hq, Tq].
  * workspace   device buffer of at least pulsar_phase2_workspace_bytes(...)
- *             bytes (may be NULL when that is 0).  Its contents on entry
- *             do not matter.
+ *             bytes (may be NULL when that is 0; few query rows over short
+ *             shards also run without it).  Its contents on entry do not
+ *             matter.
  * An empty shard (S == 0) gives lse = -inf and o = 0.
  *
  * EINVAL: negative sizes, Hq % Hkv != 0, NULL required pointers, scale not
@@ -397,8 +399,8 @@ int pulsar_phase2_query(const void* q, const void* Kg, const void* Vg, int64_t G
  * once per device on the first call made with that device current.  The
  * call allocates nothing (no hipMalloc, no library allocation).
  *
- * ETOOLARGE: pulsar_phase2_query_workspace_bytes(...) for these shapes
- *   exceeds PULSAR_STATIC_SCRATCH_BYTES (about 33 partials of 64 tokens x 32
+ * ETOOLARGE: the partials of these shapes, with longer and so fewer key ranges
+ *   where it takes them, exceed PULSAR_STATIC_SCRATCH_BYTES (about 33 partials of 64 tokens x 32
  *   heads x 128 fit, e.g. a 64-token query encoding over 16 shards).
  * Every call on one GPU uses that GPU's one array: calls that overlap in time
  * on the same GPU (different streams, or host threads without ordering) race

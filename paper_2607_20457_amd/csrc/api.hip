@@ -287,7 +287,8 @@ static int attn_splits(int n_shards, int Tq, int64_t S, int Hq, int Hkv) {
 
 static int phase2_splits(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d) {
   if (S <= 0) return 1;
-  if (decode_applies(Tq, Hq, Hkv, d)) return decode_parts(n_shards, S, Hkv);
+  if (decode_applies(Tq, Hq, Hkv, d))
+    return decode_parts(n_shards, S, Hkv, decode_min_keys(Tq * (Hq / Hkv)));
   if (packed_applies(Tq, Hq, Hkv, d)) return packed_parts(n_shards, S, Hkv);
   return attn_splits(n_shards, Tq, S, Hq, Hkv);
 }
@@ -296,10 +297,23 @@ extern "C" {
 
 size_t pulsar_phase2_workspace_bytes(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d) {
   if (n_shards < 0 || Tq < 0 || S < 0 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0 || d < 1) return 0;
+  const auto bytes = [&](int tokens, int64_t parts) {
+    return (size_t)(parts * tokens * Hq * (d + 1) * 4);
+  };
   const int ns = phase2_splits(n_shards, Tq, S, Hq, Hkv, d);
   if (ns <= 1) return 0;
-  const int64_t per = (int64_t)n_shards * ns;
-  return (size_t)(per * Tq * Hq * d * 4 + per * Hq * Tq * 4);
+  const size_t need = bytes(Tq, (int64_t)n_shards * ns);
+  if (d != 64 && d != 128) return need;
+  // A caller may size its workspace once, for the most tokens and the most and
+  // longest shards: fewer take another kernel or other key ranges.
+  const int group = Hq / Hkv;
+  const int dec = std::min(Tq, kDecodeRows / group), pk = std::min(Tq, packed_tokens(Hq, Hkv, d));
+  size_t most = need;
+  for (int tokens = dec; tokens > 0; --tokens)
+    most = std::max(most, bytes(tokens, decode_ranges_most(n_shards, S, Hkv,
+                                                           decode_min_keys(tokens * group))));
+  if (pk > dec) most = std::max(most, bytes(pk, packed_ranges_most(n_shards, S, Hkv)));
+  return most;
 }
 
 int pulsar_phase2_partial(const void* q, const void* K, const void* V, int n_shards, int Tq,
@@ -320,12 +334,13 @@ int pulsar_phase2_partial(const void* q, const void* K, const void* V, int n_sha
   if (!aligned16(q) || (S > 0 && (!aligned16(K) || !aligned16(V))) || !aligned16(o_parts))
     return PULSAR_EINVAL;
   int ns = phase2_splits(n_shards, Tq, S, Hq, Hkv, d);
-  size_t need = pulsar_phase2_workspace_bytes(n_shards, Tq, S, Hq, Hkv, d);
-  // Short shards, or enough of them to fill the chip, also run without a
+  const int64_t parts = (int64_t)n_shards * ns;
+  size_t need = ns > 1 ? (size_t)(parts * Tq * Hq * (d + 1) * 4) : 0;
+  // Short shards, or enough of them to fill the chip, also run without the
   // workspace: one range per shard.
   const bool decode = decode_applies(Tq, Hq, Hkv, d);
   const bool packed = !decode && packed_applies(Tq, Hq, Hkv, d);
-  if (workspace == nullptr &&
+  if ((workspace == nullptr || workspace_bytes < need || !aligned16(workspace)) &&
       ((decode && decode_parts(n_shards, S, Hkv, kDecodeMinKeysScarce) == 1) ||
        (packed && attn_splits(n_shards, Tq, S, Hq, Hkv) == 1))) {
     ns = 1;
@@ -397,16 +412,29 @@ inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 // one merge folds them all.  With the decode kernel (few query rows) or the
 // packed kernel (a few dozen tokens) one launch covers the ranges of every
 // shard and of the generation shard (the G appended rows and the new tokens'
-// own).  Otherwise the attention kernel
-// gives the key splits of the shards.  A generation shard of at most
-// kGenDecodeRows rows, for at most kGenDecodeQueryRows (token, head) rows
-// per KV head, then goes to the decode kernel in 32-row tiles (each token
-// limited to the rows up to its own; every tile reads the shard's K/V once,
-// so this is kept to 16 tiles).  Otherwise the attention kernel takes it:
-// key splits of the G appended rows, and one index-causal partial over the
-// new tokens' own rows.
+// own).  Otherwise the attention kernel gives the key splits of the shards.  A
+// generation shard of at most kGenDecodeRows rows, for at most
+// kGenDecodeQueryRows (token, head) rows per KV head, then goes to the decode
+// kernel in 32-row tiles (each token limited to the rows up to its own; every
+// tile reads the shard's K/V once, so this is kept to 16 tiles).  Otherwise
+// the attention kernel takes it: key splits of the G appended rows, and one
+// index-causal partial over the new tokens' own rows.
 constexpr int64_t kGenDecodeRows = 4096;
 constexpr int64_t kGenDecodeQueryRows = 512;
+
+// Keys per range of a generation shard in a decode launch, at least: as a
+// shard's, and 1024 / query_rows ranges at most, as each writes a partial of
+// all the rows (8 tokens of 4 heads, 4000 rows beside 4 x 1000 keys: 26.3 us
+// with ranges of 32 keys throughout, 23.8 with 125 here, 15.8 with the shards'
+// at 128 as well), or 16 for the more rows of a query
+// encoding (128 tokens, 3000 rows, 8 x 4096 keys: 188 us with ranges of 32
+// keys, 110 with 16 of them, 113 of 256 keys; 100 tokens, 400 rows, 4 x 2000:
+// 36.6, 36.5, 40.8).
+int gen_min_keys(int query_rows, int64_t rows, int min_keys) {
+  const int64_t keys = query_rows <= kDecodeRows ? (rows * query_rows + 1023) / 1024 : (rows + 15) / 16;
+  return (int)std::max<int64_t>(keys, min_keys);
+}
+
 struct QueryPlan {
   bool decode;      // everything in one decode launch
   bool packed;      // everything in one packed launch
@@ -422,7 +450,6 @@ QueryPlan query_plan(int n_shards, int Tq, int64_t S, int64_t G, int Hq, int Hkv
   p.decode = decode_applies(Tq, Hq, Hkv, d);
   p.packed = !p.decode && packed_applies(Tq, Hq, Hkv, d);
   if (p.packed) {
-    // the generation shard in ranges about as long as the shards'
     const int pk_keys = min_keys == kDecodeMinKeys ? kPackedMinKeys : kPackedMinKeysScarce;
     p.np_shard = packed_parts(n_shards, S, Hkv, pk_keys);
     // the generation shard in ranges about as long as the shards', in
@@ -440,12 +467,13 @@ QueryPlan query_plan(int n_shards, int Tq, int64_t S, int64_t G, int Hq, int Hkv
   p.gen_decode = p.decode || ((d == 64 || d == 128) && Hq / Hkv <= 32 && G + Tq <= kGenDecodeRows &&
                                (int64_t)Tq * (Hq / Hkv) <= kGenDecodeQueryRows);
   if (p.decode) {
+    min_keys = std::max(min_keys, decode_min_keys(Tq * (Hq / Hkv)));
     p.np_shard = decode_parts(n_shards, S, Hkv, min_keys);
   } else {
     p.np_shard = n_shards > 0 ? phase2_splits(n_shards, Tq, S, Hq, Hkv, d) : 0;
   }
   if (p.gen_decode) {
-    p.np_gen = decode_parts(1, G + Tq, Hkv, min_keys);
+    p.np_gen = decode_parts(1, G + Tq, Hkv, gen_min_keys(Tq * (Hq / Hkv), G + Tq, min_keys));
     p.parts = n_shards * p.np_shard + p.np_gen;
   } else {
     p.np_gen = G > 0 ? phase2_splits(1, Tq, G, Hq, Hkv, d) : 0;
@@ -497,7 +525,36 @@ size_t pulsar_phase2_query_workspace_bytes(int n_shards, int Tq, int64_t S, int6
                                            int Hkv, int d) {
   if (n_shards < 0 || Tq < 0 || S < 0 || G < 0 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0 || d < 1)
     return 0;
-  return parts_bytes(query_plan(n_shards, Tq, S, G, Hq, Hkv, d, kDecodeMinKeys), Tq, Hq, d);
+  const auto bytes = [&](int tokens, int64_t parts) {
+    return align16((size_t)parts * tokens * Hq * d * 4) + align16((size_t)parts * Hq * tokens * 4);
+  };
+  const QueryPlan plan = query_plan(n_shards, Tq, S, G, Hq, Hkv, d, kDecodeMinKeys);
+  size_t need = bytes(Tq, plan.parts);
+  if (Tq == 0 || (d != 64 && d != 128)) return need;
+  // A caller may size its workspace once, for the most tokens and appended
+  // rows that it will have: what fewer of them take in each kernel.
+  const int group = Hq / Hkv;
+  const int dec = std::min(Tq, kDecodeRows / group), pk = std::min(Tq, packed_tokens(Hq, Hkv, d));
+  if (!plan.decode && !plan.packed && group <= 32) {
+    const int tokens = (int)std::min<int64_t>(Tq, kGenDecodeQueryRows / group);
+    const int64_t rows = std::min(G + tokens, kGenDecodeRows);
+    const int keys = gen_min_keys(Tq * group, rows, kDecodeMinKeys);
+    need = std::max(need, bytes(tokens, (int64_t)n_shards * plan.np_shard +
+                                            decode_ranges_most(1, rows, Hkv, keys)));
+  }
+  if (pk > dec) {
+    const int64_t ranges = packed_ranges_most(n_shards, S, Hkv);
+    const int64_t own = ranges + packed_ranges_most(1, G + pk, Hkv);
+    const int64_t fits = ranges == 0 ? own : std::min<int64_t>(256 / Hkv, own);
+    need = std::max(need, bytes(pk, std::max(ranges, fits)));
+  }
+  for (int tokens = dec; tokens > 0; --tokens) {
+    const int keys = decode_min_keys(tokens * group);
+    const int gen_keys = gen_min_keys(tokens * group, G + tokens, keys);
+    need = std::max(need, bytes(tokens, decode_ranges_most(n_shards, S, Hkv, keys) +
+                                            decode_ranges_most(1, G + tokens, Hkv, gen_keys)));
+  }
+  return need;
 }
 
 }  // extern "C"

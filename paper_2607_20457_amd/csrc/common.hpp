@@ -163,7 +163,12 @@ int launch_maxidf_split(const int32_t* ids, int batch, int64_t L, int num_blocks
                         void* workspace, hipStream_t stream);
 constexpr int kDecodeMinKeys = 32;        // one step of the decode kernel
 constexpr int kDecodeMinKeysScarce = 256;  // where partials have to be few
-int decode_parts(int n_shards, int64_t S, int Hkv, int min_keys = kDecodeMinKeys);
+constexpr int kDecodeRows = 32;            // query rows per KV head, at most
+int decode_parts(int n_shards, int64_t S, int Hkv, int min_keys);
+int decode_min_keys(int query_rows);  // least keys per range worth a partial of the rows
+// The most ranges, of all shards, for up to n_shards shards of up to S keys (the
+// count itself drops where a range's length goes up to the next whole step).
+int64_t decode_ranges_most(int n_shards, int64_t S, int Hkv, int min_keys);
 bool decode_applies(int Tq, int Hq, int Hkv, int d);
 // The generation shard of a decode step, folded into the same launch: rows
 // [0, G) are the tokens appended earlier, row G + t is new token t's own, and
@@ -186,6 +191,9 @@ constexpr int kPackedMinKeys = 128;        // one step of every wave
 constexpr int kPackedMinKeysScarce = 512;  // where partials have to be few
 bool packed_applies(int Tq, int Hq, int Hkv, int d);
 int packed_parts(int n_shards, int64_t S, int Hkv, int min_keys = kPackedMinKeys);
+int64_t packed_ranges_most(int n_shards, int64_t S, int Hkv, int min_keys = kPackedMinKeys);
+// Tokens that a packed launch takes at most.
+int packed_tokens(int Hq, int Hkv, int d);
 int launch_packed(const uint16_t* q, const uint16_t* K, const uint16_t* V, int n_shards, int Tq,
                   int64_t S, int Hq, int Hkv, int d, float scale, float* o, float* lse,
                   int nparts, hipStream_t stream, const DecodeGen* gen = nullptr);

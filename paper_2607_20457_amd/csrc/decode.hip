@@ -349,8 +349,23 @@ int decode_parts(int n_shards, int64_t S, int Hkv, int min_keys) {
   return (int)((S + len - 1) / len);
 }
 
+// A range is to be worth its partial: the more query rows a KV head has, the
+// more bytes that is.  About four keys a row (launch and merge, 4 x 1000 keys of 8 KV
+// heads and 4 heads each, ranges of 32 keys / of four a row: 8 tokens 20.0 / 14.9
+// us, 4 tokens 13.4 / 12.4; 8 tokens with ranges of 256 keys 18.5), in powers
+// of two: fewer tokens then never take more bytes of partials.
+int decode_min_keys(int query_rows) {
+  return query_rows <= 8 ? kDecodeMinKeys : query_rows <= 16 ? 2 * kDecodeMinKeys : 4 * kDecodeMinKeys;
+}
+
+int64_t decode_ranges_most(int n_shards, int64_t S, int Hkv, int min_keys) {
+  if (S <= 0 || n_shards <= 0) return std::max(n_shards, 0);
+  const int64_t per_shard = std::min<int64_t>((S + min_keys - 1) / min_keys, 256);
+  return std::min<int64_t>(n_shards * per_shard, (256 * 4 + Hkv - 1) / Hkv + n_shards - 1);
+}
+
 bool decode_applies(int Tq, int Hq, int Hkv, int d) {
-  return (d == 64 || d == 128) && Tq >= 1 && (int64_t)Tq * (Hq / Hkv) <= 32;
+  return (d == 64 || d == 128) && Tq >= 1 && (int64_t)Tq * (Hq / Hkv) <= kDecodeRows;
 }
 
 int launch_decode(const uint16_t* q, const uint16_t* K, const uint16_t* V, int n_shards, int Tq,

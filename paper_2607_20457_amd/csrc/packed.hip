@@ -585,9 +585,13 @@ int launch_packed_d(const PackedArgs& a, int tiles, int64_t nwg, hipStream_t str
 // 160 / 168 us: their accumulators fill the registers.  At d = 64, 5 x 3000
 // keys of 16 heads, 2 tiles: 46.5 / 19.2 us; 16 x 2000, 16 / 8 heads, 4 tiles:
 // 38.4 / 27.9 us.
+int packed_tokens(int Hq, int Hkv, int d) {
+  const int group = Hq / Hkv, tiles = d == 64 ? 6 : 4;
+  return (d == 64 || d == 128) && group >= 1 && group <= 32 ? tiles * (32 / group) : 0;
+}
+
 bool packed_applies(int Tq, int Hq, int Hkv, int d) {
-  const int group = Hq / Hkv;
-  return (d == 64 || d == 128) && Tq >= 1 && group <= 32 && packed_tiles(Tq, group) <= (d == 64 ? 6 : 4);
+  return Tq >= 1 && Tq <= packed_tokens(Hq, Hkv, d);
 }
 
 // Keys per range when S keys are cut into nparts ranges of whole steps of all
@@ -607,6 +611,12 @@ int packed_parts(int n_shards, int64_t S, int Hkv, int min_keys) {
       std::min<int64_t>(256 / wgs, (S + min_keys - 1) / min_keys), 1);
   const int64_t len = packed_part_len(S, (int)np);
   return (int)((S + len - 1) / len);
+}
+
+int64_t packed_ranges_most(int n_shards, int64_t S, int Hkv, int min_keys) {
+  if (S <= 0 || n_shards <= 0) return std::max(n_shards, 0);
+  return std::min<int64_t>(n_shards * ((S + min_keys - 1) / min_keys),
+                           std::max(256 / Hkv, n_shards));
 }
 
 int launch_packed(const uint16_t* q, const uint16_t* K, const uint16_t* V, int n_shards, int Tq,

@@ -147,3 +147,41 @@ def test_packed_far_larger_later_score():
     vb = workload.bf16_normal(1403, (2, S, Hkv, d))
     kg, vg = (workload.bf16_normal(s, (Tq, Hkv, d)) for s in (1404, 1405))
     _run_and_check(qb, kg, vg, 0, kb, vb, "packed, far larger later score")
+
+
+@pytest.mark.parametrize("Tq,G", [
+    (40, 530),   # nine ranges of the generation shard, 64 rows each
+    (33, 0),     # two ranges, the last of one row
+    (8, 300),    # decode step: three ranges of up to 128 rows
+    (4, 61),     # 64 rows a range at least: a second range of one row
+])
+def test_generation_ranges_follow_the_tokens(Tq, G):
+    q = workload.bf16_normal(1500 + Tq, (Tq, 32, 128))
+    kg, vg = (workload.bf16_normal(s + Tq, (G + Tq, 8, 128)) for s in (1501, 1502))
+    k, v = (workload.bf16_normal(s + Tq, (2, 600, 8, 128)) for s in (1503, 1504))
+    _run_and_check(q, kg, vg, G, k, v, f"generation ranges Tq={Tq} G={G}")
+
+
+def test_workspace_sized_once_serves_smaller_steps():
+    # a loop sizes its workspace for its largest step; every smaller one, on
+    # whatever kernel and ranges, finds room in it
+    H, S, Hq, Hkv, d, G = 3, 700, 32, 8, 128, 1200
+    size = P.api._lib.lib().pulsar_phase2_query_workspace_bytes(H, 40, S, G, Hq, Hkv, d)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    def rows(*shape):
+        return torch.randn(shape, generator=g, device="cuda").bfloat16()
+    k, v = rows(H, S, Hkv, d), rows(H, S, Hkv, d)
+    kg, vg = rows(G + 40, Hkv, d), rows(G + 40, Hkv, d)
+    lib, ptr = P.api._lib.lib(), torch.Tensor.data_ptr
+    for Tq in (1, 3, 8, 9, 20, 32, 33, 40):
+        for g0 in (0, 31, 257, 1100, 1200):
+            for h, s in ((1, 64), (1, 513), (2, 700), (3, 65), (3, 512), (3, 700)):
+                q, kc, vc = rows(Tq, Hq, d), k[:h, :s].contiguous(), v[:h, :s].contiguous()
+                o = torch.empty((Tq, Hq, d), device="cuda")
+                lse = torch.empty((Hq, Tq), device="cuda")
+                assert lib.pulsar_phase2_query(
+                    ptr(q), ptr(kg), ptr(vg), g0, ptr(kc), ptr(vc), h, Tq, s, Hq, Hkv, d, 0.1,
+                    ptr(o), ptr(lse), ptr(ws), size, P.api._stream()) == 0, (Tq, g0, h, s)
+                ref = P.phase2_query(q, kg[:g0 + Tq], vg[:g0 + Tq], g0, kc, vc, softmax_scale=0.1)
+                assert torch.equal(o, ref[0]) and torch.equal(lse, ref[1]), (Tq, g0, h, s)

@@ -70,8 +70,8 @@ def test_noalloc_rejects_partials_beyond_the_scratch():
 
 def test_noalloc_takes_longer_key_ranges_where_the_scratch_needs_it():
     # 100 short shards of 32 KV heads leave room for 127 partials of 32 rows:
-    # the generation shard's rows in 32-key ranges would take 32 more, in 256-key ranges 4
-    n, S, G, Tq, H, d = 100, 40, 980, 32, 32, 128
+    # the generation shard's 4096 rows in 128-key ranges would take 32 more, in 256-key ranges 16
+    n, S, G, Tq, H, d = 100, 40, 4064, 32, 32, 128
     lib = P.api._lib.lib()
     assert lib.pulsar_phase2_query_workspace_bytes(n, Tq, S, G, H, H, d) > (64 << 20)
     q, K, V, Kg, Vg = _case(7301, n, S, G, Tq, H, H, d)
