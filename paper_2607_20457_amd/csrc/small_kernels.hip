@@ -135,9 +135,10 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(
     acc *= alpha;
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
-      const float w = p0 + u < H ? __expf(l[u] - nm_use) : 0.f;
+      const bool has = p0 + u < H && l[u] != -INFINITY;
+      const float w = has ? __expf(l[u] - nm_use) : 0.f;
       sum += w;
-      acc += w * v[u];
+      acc += w * (has ? v[u] : f32x4{0.f, 0.f, 0.f, 0.f});
     }
     m = nm;
   }
@@ -200,9 +201,10 @@ __global__ __launch_bounds__(THREADS) void lse_merge_wide_kernel(
     acc *= alpha;
 #pragma unroll
     for (int u = 0; u < CH; ++u) {
-      const float w = p0 + u * PG < H ? __expf(l[u] - use) : 0.f;
+      const bool has = p0 + u * PG < H && l[u] != -INFINITY;
+      const float w = has ? __expf(l[u] - use) : 0.f;
       sum += w;
-      acc += w * v[u];
+      acc += w * (has ? v[u] : f32x4{0.f, 0.f, 0.f, 0.f});
     }
     m = nm;
   }

@@ -187,6 +187,37 @@ def test_merge_many_parts_few_outputs(H, Tq, Hq, d):
     assert np.all(o.cpu().numpy()[0, 0] == 0) and np.isneginf(lse.cpu().numpy()[0, 0])
 
 
+@pytest.mark.parametrize("H,Tq,Hq,d", [
+    (1, 1, 4, 64), (3, 2, 8, 128), (7, 300, 2, 64),  # one thread per output
+    (8, 1, 32, 128), (70, 2, 8, 64),                  # one workgroup per row
+    (40, 700, 32, 8),                                 # many parts, many outputs
+])
+def test_merge_ignores_the_output_of_a_missing_part(H, Tq, Hq, d):
+    # l = -inf means that the part contributes nothing, whatever its o holds
+    # (an allocation that no kernel wrote): the result is that of zeros there.
+    # One row with a part left at the last index, whose re-read copies must
+    # not turn an infinite o into NaN, and one without any part.
+    rng = np.random.default_rng(100 + H)
+    op = rng.standard_normal((H, Tq, Hq, d)).astype(np.float32)
+    lp = (rng.standard_normal((H, Hq, Tq)) * 3).astype(np.float32)
+    lp[::2] = -np.inf
+    lp[H - 1] = 1.0
+    lp[:, 0, 0] = -np.inf
+    gone = np.isneginf(lp).transpose(0, 2, 1)
+    zeroed = np.where(gone[..., None], np.float32(0), op)
+    for junk in (np.nan, np.inf):
+        bad = np.where(gone[..., None], np.float32(junk), op)
+        o, lse = P.lse_merge(torch.from_numpy(bad).cuda(), torch.from_numpy(lp).cuda())
+        r, rl = P.lse_merge(torch.from_numpy(zeroed).cuda(), torch.from_numpy(lp).cuda())
+        torch.cuda.synchronize()
+        assert torch.equal(o, r) and torch.equal(lse, rl)
+        assert (o[0, 0] == 0).all() and torch.isneginf(lse[0, 0])
+    op[H - 1, 0, 1] = np.inf
+    o, _ = P.lse_merge(torch.from_numpy(op).cuda(), torch.from_numpy(lp).cuda())
+    torch.cuda.synchronize()
+    assert (o[0, 1].cpu().numpy() == np.inf).all()
+
+
 @pytest.mark.parametrize("Tq,S", [(1, 200), (20, 400)])
 def test_short_shards_need_no_workspace(Tq, S):
     # one key range per shard where the caller brings no workspace, whatever
