@@ -270,7 +270,7 @@ int pulsar_phase1_attn(const void* Q, const void* K, const void* V, int batch, i
 // launch has enough workgroups to cover the chip; the partials of a shard are
 // then merged with the same online-softmax merge as the shards themselves.
 static int attn_splits(int n_shards, int Tq, int64_t S, int Hq, int Hkv) {
-  if (S <= 0) return 1;
+  if (S <= 0 || n_shards <= 0 || Tq <= 0) return 1;
   const int group = Hq / Hkv;
   const int heads_per_wg = group >= 4 ? 4 : group;
   const int rows_per_wg = attn_rows_per_wg(group, false);

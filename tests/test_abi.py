@@ -200,6 +200,16 @@ def test_phase2_query_validation():
     assert lib.pulsar_phase2_workspace_bytes(0, 1, 512, 32, 8, 128) == 0
 
 
+def test_phase2_sizes_of_nothing():
+    # no shards or no tokens: the size queries answer (they divided by zero)
+    lib = _lib.lib()
+    for Tq in (0, 1, 20, 64, 300):
+        assert lib.pulsar_phase2_workspace_bytes(0, Tq, 8192, 32, 8, 128) == 0
+    for n in (0, 1, 16):
+        assert lib.pulsar_phase2_workspace_bytes(n, 0, 8192, 32, 8, 128) == 0
+        assert lib.pulsar_phase2_query_workspace_bytes(n, 0, 8192, 10, 32, 8, 128) == 0
+
+
 def test_phase2_query_noalloc_validation():
     # Host-side checks come before any device call: bad arguments, no work
     # and partials beyond the static scratch all return without touching a GPU.
