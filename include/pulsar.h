@@ -301,8 +301,8 @@ int pulsar_phase1_attn(const void* Q, const void* K, const void* V, int batch, i
 
 /*
  * Device workspace, in bytes, that pulsar_phase2_partial needs for these
- * shapes, and for fewer tokens over no more and no longer shards (0 when these
- * shapes need none).  Host-only.
+ * shapes (0 when they need none).  Not monotone: other shapes, also smaller
+ * ones, ask again.  Host-only.
  */
 size_t pulsar_phase2_workspace_bytes(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d);
 
@@ -320,9 +320,9 @@ size_t pulsar_phase2_workspace_bytes(int n_shards, int Tq, int64_t S, int Hq, in
  * o_parts     out float32 [n_shards, Tq, Hq, d].
  * lse_parts   out float32 [n_shards, Hq, Tq].
  * workspace   device buffer of at least pulsar_phase2_workspace_bytes(...)
- *             bytes (may be NULL when that is 0; few query rows over short
- *             shards also run without it).  Its contents on entry do not
- *             matter.
+ *             bytes (may be NULL when that is 0).  Few query rows also run,
+ *             in longer key ranges, with a smaller one, and without any over
+ *             short shards.  Its contents on entry do not matter.
  * An empty shard (S == 0) gives lse = -inf and o = 0.
  *
  * EINVAL: negative sizes, Hq % Hkv != 0, NULL required pointers, scale not

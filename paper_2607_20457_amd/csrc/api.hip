@@ -293,27 +293,23 @@ static int phase2_splits(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d
   return attn_splits(n_shards, Tq, S, Hq, Hkv);
 }
 
+// The longer ranges of a call whose workspace, sized for other shapes, does not
+// hold those: at least 256 keys in the decode kernel (counted before they are
+// made whole steps), else the attention kernel's splits.  The size query counts
+// them too: one call's size serves another wherever these ranges fit it.
+static int phase2_splits_few(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d) {
+  if (S <= 0) return 1;
+  if (decode_applies(Tq, Hq, Hkv, d)) return decode_waves(n_shards, S, Hkv, kDecodeMinKeysScarce);
+  return attn_splits(n_shards, Tq, S, Hq, Hkv);
+}
+
 extern "C" {
 
 size_t pulsar_phase2_workspace_bytes(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d) {
   if (n_shards < 0 || Tq < 0 || S < 0 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0 || d < 1) return 0;
-  const auto bytes = [&](int tokens, int64_t parts) {
-    return (size_t)(parts * tokens * Hq * (d + 1) * 4);
-  };
-  const int ns = phase2_splits(n_shards, Tq, S, Hq, Hkv, d);
-  if (ns <= 1) return 0;
-  const size_t need = bytes(Tq, (int64_t)n_shards * ns);
-  if (d != 64 && d != 128) return need;
-  // A caller may size its workspace once, for the most tokens and the most and
-  // longest shards: fewer take another kernel or other key ranges.
-  const int group = Hq / Hkv;
-  const int dec = std::min(Tq, kDecodeRows / group), pk = std::min(Tq, packed_tokens(Hq, Hkv, d));
-  size_t most = need;
-  for (int tokens = dec; tokens > 0; --tokens)
-    most = std::max(most, bytes(tokens, decode_ranges_most(n_shards, S, Hkv,
-                                                           decode_min_keys(tokens * group))));
-  if (pk > dec) most = std::max(most, bytes(pk, packed_ranges_most(n_shards, S, Hkv)));
-  return most;
+  const int64_t ns = std::max(phase2_splits(n_shards, Tq, S, Hq, Hkv, d),
+                              phase2_splits_few(n_shards, Tq, S, Hq, Hkv, d));
+  return ns > 1 ? (size_t)(n_shards * ns * Tq * Hq * (d + 1) * 4) : 0;
 }
 
 int pulsar_phase2_partial(const void* q, const void* K, const void* V, int n_shards, int Tq,
@@ -333,21 +329,22 @@ int pulsar_phase2_partial(const void* q, const void* K, const void* V, int n_sha
   if (S > 0 && (K == nullptr || V == nullptr)) return PULSAR_EINVAL;
   if (!aligned16(q) || (S > 0 && (!aligned16(K) || !aligned16(V))) || !aligned16(o_parts))
     return PULSAR_EINVAL;
-  int ns = phase2_splits(n_shards, Tq, S, Hq, Hkv, d);
-  const int64_t parts = (int64_t)n_shards * ns;
-  size_t need = ns > 1 ? (size_t)(parts * Tq * Hq * (d + 1) * 4) : 0;
-  // Short shards, or enough of them to fill the chip, also run without the
-  // workspace: one range per shard.
   const bool decode = decode_applies(Tq, Hq, Hkv, d);
   const bool packed = !decode && packed_applies(Tq, Hq, Hkv, d);
-  if ((workspace == nullptr || workspace_bytes < need || !aligned16(workspace)) &&
-      ((decode && decode_parts(n_shards, S, Hkv, kDecodeMinKeysScarce) == 1) ||
-       (packed && attn_splits(n_shards, Tq, S, Hq, Hkv) == 1))) {
-    ns = 1;
-    need = 0;
+  // The key ranges that the call prefers, or else the fewer ones of a workspace
+  // sized for other shapes (none where that is one range per shard).
+  int ns = phase2_splits(n_shards, Tq, S, Hq, Hkv, d);
+  const auto room = [&](int ranges) {
+    return ranges == 1 ||
+           (workspace != nullptr && aligned16(workspace) &&
+            workspace_bytes >= (size_t)((int64_t)n_shards * ranges * Tq * Hq * (d + 1) * 4));
+  };
+  if (!room(ns)) {
+    ns = phase2_splits_few(n_shards, Tq, S, Hq, Hkv, d);
+    if (decode) ns = decode_ranges(S, ns);
+    else if (packed) ns = packed_ranges(S, ns);
+    if (!room(ns)) return PULSAR_EWORKSPACE;
   }
-  if (need > 0 && (workspace == nullptr || workspace_bytes < need || !aligned16(workspace)))
-    return PULSAR_EWORKSPACE;
 
   float* ws_o = static_cast<float*>(workspace);
   float* ws_l = ws_o + (int64_t)n_shards * ns * Tq * Hq * d;

@@ -165,6 +165,8 @@ constexpr int kDecodeMinKeys = 32;        // one step of the decode kernel
 constexpr int kDecodeMinKeysScarce = 256;  // where partials have to be few
 constexpr int kDecodeRows = 32;            // query rows per KV head, at most
 int decode_parts(int n_shards, int64_t S, int Hkv, int min_keys);
+int decode_waves(int n_shards, int64_t S, int Hkv, int min_keys);
+int decode_ranges(int64_t S, int nparts);
 int decode_min_keys(int query_rows);  // least keys per range worth a partial of the rows
 // The most ranges, of all shards, for up to n_shards shards of up to S keys (the
 // count itself drops where a range's length goes up to the next whole step).
@@ -191,6 +193,7 @@ constexpr int kPackedMinKeys = 128;        // one step of every wave
 constexpr int kPackedMinKeysScarce = 512;  // where partials have to be few
 bool packed_applies(int Tq, int Hq, int Hkv, int d);
 int packed_parts(int n_shards, int64_t S, int Hkv, int min_keys = kPackedMinKeys);
+int packed_ranges(int64_t S, int nparts);
 int64_t packed_ranges_most(int n_shards, int64_t S, int Hkv, int min_keys = kPackedMinKeys);
 // Tokens that a packed launch takes at most.
 int packed_tokens(int Hq, int Hkv, int d);

@@ -342,10 +342,20 @@ int decode_part_len(int64_t S, int nparts) {
 // range: 17.5 / 14.0 / 11.5 / 10.6 us for the launch and the merge).
 int decode_parts(int n_shards, int64_t S, int Hkv, int min_keys) {
   if (S <= 0 || n_shards <= 0 || Hkv <= 0) return 1;
+  return decode_ranges(S, decode_waves(n_shards, S, Hkv, min_keys));
+}
+
+// The same before the ranges are made whole steps.
+int decode_waves(int n_shards, int64_t S, int Hkv, int min_keys) {
+  if (S <= 0 || n_shards <= 0 || Hkv <= 0) return 1;
   const int64_t waves = (int64_t)n_shards * Hkv;
-  int64_t np = (256 * 4 + waves - 1) / waves;
-  np = std::min(std::min<int64_t>(np, (S + min_keys - 1) / min_keys), (int64_t)256);
-  const int64_t len = decode_part_len(S, (int)np);
+  const int64_t np = (256 * 4 + waves - 1) / waves;
+  return (int)std::min({np, (S + min_keys - 1) / min_keys, (int64_t)256});
+}
+
+// The ranges that `nparts` come to in whole steps.
+int decode_ranges(int64_t S, int nparts) {
+  const int64_t len = decode_part_len(S, nparts);
   return (int)((S + len - 1) / len);
 }
 
@@ -361,7 +371,7 @@ int decode_min_keys(int query_rows) {
 int64_t decode_ranges_most(int n_shards, int64_t S, int Hkv, int min_keys) {
   if (S <= 0 || n_shards <= 0) return std::max(n_shards, 0);
   const int64_t per_shard = std::min<int64_t>((S + min_keys - 1) / min_keys, 256);
-  return std::min<int64_t>(n_shards * per_shard, (256 * 4 + Hkv - 1) / Hkv + n_shards - 1);
+  return std::min<int64_t>(n_shards * per_shard, (256 * 4 + (int64_t)Hkv - 1) / Hkv + n_shards - 1);
 }
 
 bool decode_applies(int Tq, int Hq, int Hkv, int d) {

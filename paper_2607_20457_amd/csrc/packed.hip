@@ -609,7 +609,12 @@ int packed_parts(int n_shards, int64_t S, int Hkv, int min_keys) {
   const int64_t wgs = (int64_t)n_shards * Hkv;
   const int64_t np = std::max<int64_t>(
       std::min<int64_t>(256 / wgs, (S + min_keys - 1) / min_keys), 1);
-  const int64_t len = packed_part_len(S, (int)np);
+  return packed_ranges(S, (int)np);
+}
+
+// The ranges that `nparts` come to in whole steps.
+int packed_ranges(int64_t S, int nparts) {
+  const int64_t len = packed_part_len(S, nparts);
   return (int)((S + len - 1) / len);
 }
 

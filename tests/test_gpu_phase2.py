@@ -237,3 +237,30 @@ def test_short_shards_need_no_workspace(Tq, S):
     for h in range(H):
         ref = attention.partial_attention(f64(q), f64(k[h]), f64(v[h]), 1 / math.sqrt(d))
         check_attention(o[h].cpu().numpy(), lse[h].cpu().numpy(), *ref, f"shard {h}")
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,sized,call", [
+    (16, 16, 64, (6, 4, 2929), (3, 5, 638)),   # decode kernel: ranges of 256 keys
+    (8, 2, 128, (6, 61, 1927), (5, 32, 2846)),  # packed kernel: the attention kernel's splits
+])
+def test_workspace_of_other_shapes(Hq, Hkv, d, sized, call):
+    # (shards, tokens, keys).  A workspace sized for other shapes that does not
+    # hold the preferred key ranges, but fewer and longer ones: the call takes
+    # those.  (It was refused.)
+    H, Tq, S = call
+    lib = P.api._lib.lib()
+    size = lib.pulsar_phase2_workspace_bytes(*sized, Hq, Hkv, d)
+    assert 0 < size < lib.pulsar_phase2_workspace_bytes(H, Tq, S, Hq, Hkv, d)
+    q = workload.bf16_normal(71 + Tq, (Tq, Hq, d))
+    k, v = _shards(H, S, Hkv, d, 72 + S)
+    dq, dk, dv = to_dev_bf16(q), to_dev_bf16(k), to_dev_bf16(v)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    o = torch.empty((H, Tq, Hq, d), device="cuda")
+    lse = torch.empty((H, Hq, Tq), device="cuda")
+    assert lib.pulsar_phase2_partial(dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), H, Tq, S, Hq, Hkv,
+                                     d, 1 / math.sqrt(d), o.data_ptr(), lse.data_ptr(),
+                                     ws.data_ptr(), size, P.api._stream()) == 0
+    torch.cuda.synchronize()
+    for h in range(H):
+        ref = attention.partial_attention(f64(q), f64(k[h]), f64(v[h]), 1 / math.sqrt(d))
+        check_attention(o[h].cpu().numpy(), lse[h].cpu().numpy(), *ref, f"shard {h}")
