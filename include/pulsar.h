@@ -370,7 +370,9 @@ int pulsar_lse_merge(const float* o_parts, const float* lse_parts, int H, int Tq
  *           n_shards == 0 or S == 0).
  * o         out float32 [Tq, Hq, d];  lse out float32 [Hq, Tq], nullable.
  * workspace device buffer of at least pulsar_phase2_query_workspace_bytes
- *           bytes, 16-byte aligned; contents on entry do not matter.
+ *           bytes, 16-byte aligned; contents on entry do not matter.  The size
+ *           never drops when n_shards, Tq, S or G grows, so a loop may size its
+ *           workspace once, for the most of each.
  * Query encoding: G = 0, Tq = query length.  Decode step: Tq = 1, G = the
  * number of query and generated tokens before it.
  *

@@ -428,6 +428,7 @@ constexpr int64_t kGenDecodeQueryRows = 512;
 // keys, 110 with 16 of them, 113 of 256 keys; 100 tokens, 400 rows, 4 x 2000:
 // 36.6, 36.5, 40.8).
 int gen_min_keys(int query_rows, int64_t rows, int min_keys) {
+  rows = std::min<int64_t>(rows, (int64_t)1 << 30);  // (the size query takes any)
   const int64_t keys = query_rows <= kDecodeRows ? (rows * query_rows + 1023) / 1024 : (rows + 15) / 16;
   return (int)std::max<int64_t>(keys, min_keys);
 }
@@ -479,6 +480,24 @@ QueryPlan query_plan(int n_shards, int Tq, int64_t S, int64_t G, int Hq, int Hkv
   return p;
 }
 
+// The most ranges of a generation shard of up to `rows` rows in a decode launch.
+int64_t gen_ranges_most(int query_rows, int64_t rows, int Hkv, int min_keys) {
+  const int64_t cap = query_rows <= kDecodeRows ? (1023 + query_rows) / query_rows : 16;
+  return std::min({(rows + min_keys - 1) / min_keys, cap, (int64_t)(1023 + Hkv) / Hkv, (int64_t)256});
+}
+
+// The most key splits of up to n_shards shards of up to S keys in attention
+// launches of `tiles` row tiles, head slices and KV heads: not those of the
+// most shards, as fewer are cut the finer.
+int64_t attn_splits_most(int n_shards, int64_t tiles, int64_t S) {
+  const int64_t round = (256 + tiles - 1) / tiles;  // splits of one shard, if long
+  const int64_t by_len = std::min<int64_t>((S + 511) / 512, 64);
+  int64_t most = n_shards;
+  for (int64_t n = 1; n <= std::min<int64_t>(n_shards, round); ++n)
+    most = std::max(most, n * std::min((round + n - 1) / n, by_len));
+  return most;
+}
+
 // Workspace of a plan's partials: o, then lse, each 16-byte aligned.
 size_t parts_bytes(const QueryPlan& plan, int Tq, int Hq, int d) {
   const size_t parts = (size_t)plan.parts;
@@ -528,28 +547,37 @@ size_t pulsar_phase2_query_workspace_bytes(int n_shards, int Tq, int64_t S, int6
   const QueryPlan plan = query_plan(n_shards, Tq, S, G, Hq, Hkv, d, kDecodeMinKeys);
   size_t need = bytes(Tq, plan.parts);
   if (Tq == 0 || (d != 64 && d != 128)) return need;
-  // A caller may size its workspace once, for the most tokens and appended
-  // rows that it will have: what fewer of them take in each kernel.
+  // A caller may size its workspace once, for the most tokens, appended rows and
+  // shards, and the longest: what any step with no more of each takes, in
+  // whichever kernel.  Every bound below grows with each of them.
   const int group = Hq / Hkv;
   const int dec = std::min(Tq, kDecodeRows / group), pk = std::min(Tq, packed_tokens(Hq, Hkv, d));
-  if (!plan.decode && !plan.packed && group <= 32) {
-    const int tokens = (int)std::min<int64_t>(Tq, kGenDecodeQueryRows / group);
-    const int64_t rows = std::min(G + tokens, kGenDecodeRows);
-    const int keys = gen_min_keys(Tq * group, rows, kDecodeMinKeys);
-    need = std::max(need, bytes(tokens, (int64_t)n_shards * plan.np_shard +
-                                            decode_ranges_most(1, rows, Hkv, keys)));
-  }
-  if (pk > dec) {
-    const int64_t ranges = packed_ranges_most(n_shards, S, Hkv);
-    const int64_t own = ranges + packed_ranges_most(1, G + pk, Hkv);
-    const int64_t fits = ranges == 0 ? own : std::min<int64_t>(256 / Hkv, own);
-    need = std::max(need, bytes(pk, std::max(ranges, fits)));
-  }
   for (int tokens = dec; tokens > 0; --tokens) {
     const int keys = decode_min_keys(tokens * group);
-    const int gen_keys = gen_min_keys(tokens * group, G + tokens, keys);
     need = std::max(need, bytes(tokens, decode_ranges_most(n_shards, S, Hkv, keys) +
-                                            decode_ranges_most(1, G + tokens, Hkv, gen_keys)));
+                                            gen_ranges_most(tokens * group, G + tokens, Hkv, keys)));
+  }
+  if (pk > dec) {
+    // the generation shard's ranges come on top only up to a full chip
+    const int64_t ranges = packed_ranges_most(n_shards, S, Hkv);
+    const int64_t gen = packed_ranges_most(1, G + pk, Hkv);
+    need = std::max(need, bytes(pk, std::max({ranges, gen, std::min<int64_t>(256 / Hkv, ranges + gen)})));
+  }
+  // The attention kernel, by row tiles: the fewer, the more splits.  (Beyond one
+  // workgroup per compute unit and the generation shard's decode launch the
+  // number of partials stays, so the most tokens take the most bytes.)
+  const int slices = group / (group >= 4 ? 4 : group);
+  const int64_t tile = attn_rows_per_wg(group, false), tiles = (Tq + tile - 1) / tile;
+  const int64_t vary = std::max<int64_t>(256 / (slices * Hkv), kGenDecodeQueryRows / (group * tile)) + 1;
+  for (int64_t t = 1; t <= tiles; t = t == vary ? std::max(tiles, t + 1) : t + 1) {
+    const int tokens = (int)std::min<int64_t>(Tq, t * tile);
+    if (tokens <= dec) continue;
+    const int64_t wgs = t * slices * Hkv;
+    int64_t gen = 1 + (G > 0 ? attn_splits_most(1, wgs, G) : 0);
+    if (group <= 32 && ((t - 1) * tile + 1) * group <= kGenDecodeQueryRows)
+      gen = std::max(gen, gen_ranges_most(kDecodeRows + 1, std::min(G + tokens, kGenDecodeRows), Hkv,
+                                          kDecodeMinKeys));
+    need = std::max(need, bytes(tokens, attn_splits_most(n_shards, wgs, S) + gen));
   }
   return need;
 }

@@ -210,6 +210,33 @@ def test_phase2_sizes_of_nothing():
         assert lib.pulsar_phase2_query_workspace_bytes(n, 0, 8192, 10, 32, 8, 128) == 0
 
 
+@pytest.mark.parametrize("Hq,Hkv,d", [(32, 8, 128), (8, 2, 128), (4, 1, 64), (16, 16, 64),
+                                      (16, 8, 64), (64, 8, 128), (128, 2, 64)])
+def test_phase2_query_size_never_drops(Hq, Hkv, d):
+    # A loop sizes its workspace once: a step with fewer tokens, appended rows or
+    # shards, or shorter ones, may take another kernel or more key ranges, and
+    # its own size is never above the larger step's.  Every axis in turn, over
+    # the edges of the kernels' token limits, row tiles and range lengths.
+    q = _lib.lib().pulsar_phase2_query_workspace_bytes
+    tokens = [1, 2, 4, 5, 8, 9, 16, 17, 24, 32, 33, 48, 49, 63, 64, 65, 96, 97, 109, 128, 129, 172,
+              192, 193, 256, 257, 320, 512, 513, 800]
+    lengths = [0, 1, 31, 32, 33, 128, 129, 255, 256, 257, 512, 513, 700, 1021, 4096, 8192, 10846,
+               20000]
+    shards = list(range(0, 21)) + [31, 32, 33, 64, 100, 256, 257]
+    rows = [0, 1, 31, 32, 33, 255, 257, 1000, 2000, 3967, 4064, 4096, 8192, 9000, 33000]
+    axes = (shards, tokens, lengths, rows)
+    for n in (1, 3, 4, 16):
+        for Tq in (1, 8, 31, 40, 64, 65, 129, 172, 300):
+            for S in (200, 700, 8192, 10846):
+                for G in (0, 500, 4000):
+                    base = (n, Tq, S, G)
+                    for a, values in enumerate(axes):
+                        size = [q(*base[:a], x, *base[a + 1:], Hq, Hkv, d) for x in values]
+                        assert size == sorted(size), (base, a)
+    assert q(1, 128, 8192, 0, 32, 8, 128) <= q(1, 129, 8192, 0, 32, 8, 128)
+    assert q(3, 109, 10846, 0, 32, 8, 128) <= q(3, 172, 10846, 0, 32, 8, 128)
+
+
 def test_phase2_query_noalloc_validation():
     # Host-side checks come before any device call: bad arguments, no work
     # and partials beyond the static scratch all return without touching a GPU.

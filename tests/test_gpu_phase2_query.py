@@ -185,3 +185,29 @@ def test_workspace_sized_once_serves_smaller_steps():
                     ptr(o), ptr(lse), ptr(ws), size, P.api._stream()) == 0, (Tq, g0, h, s)
                 ref = P.phase2_query(q, kg[:g0 + Tq], vg[:g0 + Tq], g0, kc, vc, softmax_scale=0.1)
                 assert torch.equal(o, ref[0]) and torch.equal(lse, ref[1]), (Tq, g0, h, s)
+
+
+@pytest.mark.parametrize("H,S,most,steps", [
+    (1, 8192, 129, (128, 65, 64, 33, 1)),   # fewer row tiles take more key splits
+    (3, 10846, 172, (109, 9, 8)),           # and more generation ranges
+])
+def test_workspace_of_the_attention_kernel_serves_smaller_steps(H, S, most, steps):
+    Hq, Hkv, d = 32, 8, 128
+    size = P.api._lib.lib().pulsar_phase2_query_workspace_bytes(H, most, S, 0, Hq, Hkv, d)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(6)
+    def rows(*shape):
+        return torch.randn(shape, generator=g, device="cuda").bfloat16()
+    k, v = rows(H, S, Hkv, d), rows(H, S, Hkv, d)
+    lib, ptr = P.api._lib.lib(), torch.Tensor.data_ptr
+    for Tq in (most,) + steps:
+        for h in range(1, H + 1):
+            q, kg, vg = rows(Tq, Hq, d), rows(Tq, Hkv, d), rows(Tq, Hkv, d)
+            o = torch.empty((Tq, Hq, d), device="cuda")
+            lse = torch.empty((Hq, Tq), device="cuda")
+            assert lib.pulsar_phase2_query(
+                ptr(q), ptr(kg), ptr(vg), 0, ptr(k), ptr(v), h, Tq, S, Hq, Hkv, d, 0.1,
+                ptr(o), ptr(lse), ptr(ws), size, P.api._stream()) == 0, (Tq, h)
+            ref = P.phase2_query(q, kg, vg, 0, k[:h], v[:h], softmax_scale=0.1)
+            assert torch.equal(o, ref[0]) and torch.equal(lse, ref[1]), (Tq, h)
+    torch.cuda.synchronize()
