@@ -425,6 +425,12 @@ void attn_fwd_kernel(KernelArgs ka) {
   };
 
 
+  // KSPLIT: a row may see no key of group 1's first tile, and then none of its
+  // later ones.  Its reference is 0 throughout, against which masked scores
+  // weigh 0 (against -inf they would be NaN).
+  auto no_key = [&](int t) {
+    return KSPLIT && tile_key(0) > min(row0 + t * 32 + l32, kv_end - 1);
+  };
   auto reset = [&]() {
 #pragma unroll
     for (int e = 0; e < DT; ++e)
@@ -432,9 +438,7 @@ void attn_fwd_kernel(KernelArgs ka) {
       for (int t = 0; t < QT; ++t) acc[e][t] = f32x16{};
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
-      // (finite in the key-split form, where a row may see no key of group 1:
-      // its weights are then 0, not NaN)
-      m_ref[t] = KSPLIT ? -0x1p100f : -INFINITY;
+      m_ref[t] = no_key(t) ? 0.f : -INFINITY;
       l_run[t] = 0.f;
 #pragma unroll
       for (int j = 0; j < NSUM; ++j) lr_run[t][j] = 0.f;
@@ -610,12 +614,7 @@ void attn_fwd_kernel(KernelArgs ka) {
         }
       } else if (m == 0) {  // half 0 of tile 0 always has a visible key
 #pragma unroll
-        for (int t = 0; t < QT; ++t) {
-          m_ref[t] = row_max(S[0][t]);
-          // (KSPLIT: nor does a row that sees no key of group 1's first tile
-          // see one of its later tiles; any reference gives them weight 0)
-          if (KSPLIT && key_of(0, 0) > min(row0 + t * 32 + l32, kv_end - 1)) m_ref[t] = 0.f;
-        }
+        for (int t = 0; t < QT; ++t) m_ref[t] = no_key(t) ? 0.f : row_max(S[0][t]);
       }
       weights(S[0], P[0]);
       weights(S[1], P[1]);

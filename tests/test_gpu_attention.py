@@ -444,3 +444,33 @@ def test_key_split_far_larger_later_score(key):
     v = workload.bf16_normal(9103, (1, 512, 1, 64))
     _full_check(cfg, 0, P.PREFIX_SUMMARY, None, workload.f32_to_bf16_bits(q),
                 workload.f32_to_bf16_bits(k), v)
+
+
+@pytest.mark.parametrize("row", [300, 400])
+def test_key_split_exact_pass_of_a_very_low_row(row):
+    # Every score of one row is -2^110 (times a power-of-two scale, so that each
+    # product is exact and the row's weights are equal), while another row of
+    # its workgroup forces the exact pass: the running reference has to start
+    # below any score.  The row's output is the mean of the V that it sees.
+    n, spike, other = 512, 200, row + 10
+    scale = next(float(x) for u in range(-4, 5)
+                 for x in [np.float32(0.125 * math.log(2)) * np.float32(1 + u * 2.0 ** -23)]
+                 if x * np.float32(1.4426950408889634) == np.float32(0.125))
+    q = workload.bf16_bits_to_f32(workload.bf16_normal(9201, (1, n, 1, 64))).copy()
+    k = workload.bf16_bits_to_f32(workload.bf16_normal(9202, (1, n, 1, 64))).copy()
+    q[..., :2] = 0
+    k[..., 0], k[..., 1] = 1, 0
+    q[0, row], q[0, row, 0, 0] = 0, -2.0 ** 110
+    q[0, other, 0, 1], k[0, spike, 0, 1] = 64, 64
+    qb, kb = workload.f32_to_bf16_bits(q), workload.f32_to_bf16_bits(k)
+    vb = workload.bf16_normal(9203, (1, n, 1, 64))
+    o, lse = P.phase1_attn(to_dev_bf16(qb), to_dev_bf16(kb), to_dev_bf16(vb), 1, 0, 0, 16, 0, None,
+                           softmax_scale=scale)
+    torch.cuda.synchronize()
+    o, lse = o[0].cpu().numpy(), lse[0].cpu().numpy()
+    o_ref, lse_ref = attention.phase1_attention(f64(qb[0]), f64(kb[0]), f64(vb[0]), np.arange(n),
+                                                scale)
+    np.testing.assert_allclose(o[row, 0], f64(vb[0])[:row + 1, 0].mean(axis=0), atol=1e-5)
+    assert np.isfinite(lse[0, row]) and abs(lse[0, row] / lse_ref[0, row] - 1) < 1e-6
+    rest = np.arange(n) != row
+    check_attention(o[rest], lse[:, rest], o_ref[rest], lse_ref[:, rest], "the other rows")
