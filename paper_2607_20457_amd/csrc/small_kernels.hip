@@ -1,5 +1,7 @@
 // Bandwidth-bound helper kernels: the materialised Eq. 3 position map, the
 // KV(B_i) retention copy, and the Phase-2 online-softmax merge.
+#include <type_traits>
+
 #include "common.hpp"
 
 // ---------------------------------------------------------------------------
@@ -87,12 +89,21 @@ int launch_idf_fill(float* idf, int64_t n, int num_blocks, hipStream_t stream) {
 }
 
 // ---------------------------------------------------------------------------
+// (may also say so of opposite infinities)
+__device__ __forceinline__ bool is_nan(f32x4 x) {
+  const float s = (x[0] + x[1]) + (x[2] + x[3]);
+  return s != s;
+}
+
 // Online-softmax merge (Appendix "Phase 2 Distributed Softmax Merge").
 // Thread = four consecutive head_dim entries of one (z, query, head).  One
 // pass over the parts, CH at a time (2, 4 or 8: the fewest that cover H, up
 // to 8) with all their loads issued together: the running maximum m,
 // s = sum_h exp(l_h - m) and a = sum_h exp(l_h - m) o_h are rescaled when m
-// rises; then l = m + ln s and o = a / s.  -inf partials weigh zero.
+// rises; then l = m + ln s and o = a / s.  -inf partials weigh zero, and what
+// their o holds must not count either: where a zero weight has met a NaN or an
+// infinity there (so that a is NaN), the pass is repeated with such parts left
+// out.  (To leave them out at once costs every merge 3 to 6 %.)
 template <int CH>
 __global__ __launch_bounds__(256) void lse_merge_kernel(
     const float* __restrict__ o_parts, const float* __restrict__ lse_parts, int H, int Tq, int Hq,
@@ -110,38 +121,44 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(
   const float* lp = lse_parts + z * (int64_t)H * part_lstride + (int64_t)h * Tq + q;
   const int64_t orow = (((int64_t)q * Hq + h) * d4 + dv);
   const f32x4* op = reinterpret_cast<const f32x4*>(o_parts) + z * (int64_t)H * (part_ostride / 4);
-  float m = -INFINITY, sum = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int p0 = 0; p0 < H; p0 += CH) {
-    float l[CH];
-    f32x4 v[CH];
+  float m, sum;
+  f32x4 acc;
+  auto fold = [&](auto leave_out) {
+    m = -INFINITY, sum = 0.f;
+    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0; p0 < H; p0 += CH) {
+      float l[CH];
+      f32x4 v[CH];
 #pragma unroll
-    for (int u = 0; u < CH; ++u) {
-      const int p = min(p0 + u, H - 1);  // a part past the last re-reads it, weighing zero
-      l[u] = lp[p * part_lstride];
-      v[u] = op[p * (part_ostride / 4) + orow];
+      for (int u = 0; u < CH; ++u) {
+        const int p = min(p0 + u, H - 1);  // a part past the last re-reads it, weighing zero
+        l[u] = lp[p * part_lstride];
+        v[u] = op[p * (part_ostride / 4) + orow];
+      }
+      float cm = -INFINITY;
+#pragma unroll
+      for (int u = 0; u < CH; ++u)
+        if (p0 + u < H) cm = fmaxf(cm, l[u]);
+      // branch-free, so that all 2 CH loads are issued before the first
+      // wait; with no finite partial yet the weights are taken against 0 and
+      // come out 0
+      const float nm = fmaxf(m, cm);
+      const float nm_use = nm == -INFINITY ? 0.f : nm;
+      const float alpha = __expf(m - nm_use);  // 0 while m is -inf
+      sum *= alpha;
+      acc *= alpha;
+#pragma unroll
+      for (int u = 0; u < CH; ++u) {
+        const float w = p0 + u < H ? __expf(l[u] - nm_use) : 0.f;
+        sum += w;
+        if (decltype(leave_out)::value && (p0 + u >= H || l[u] == -INFINITY)) continue;
+        acc += w * v[u];
+      }
+      m = nm;
     }
-    float cm = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < CH; ++u)
-      if (p0 + u < H) cm = fmaxf(cm, l[u]);
-    // branch-free, so that all 2 CH loads are issued before the first
-    // wait; with no finite partial yet the weights are taken against 0 and
-    // come out 0
-    const float nm = fmaxf(m, cm);
-    const float nm_use = nm == -INFINITY ? 0.f : nm;
-    const float alpha = __expf(m - nm_use);  // 0 while m is -inf
-    sum *= alpha;
-    acc *= alpha;
-#pragma unroll
-    for (int u = 0; u < CH; ++u) {
-      const bool has = p0 + u < H && l[u] != -INFINITY;
-      const float w = has ? __expf(l[u] - nm_use) : 0.f;
-      sum += w;
-      acc += w * (has ? v[u] : f32x4{0.f, 0.f, 0.f, 0.f});
-    }
-    m = nm;
-  }
+  };
+  fold(std::false_type{});
+  if (is_nan(acc)) fold(std::true_type{});
   float ell = -INFINITY;
   if (m != -INFINITY) {
     ell = m + __logf(sum);
@@ -153,10 +170,11 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(
 
 // The same merge with one workgroup per output row (grid.y: DL groups of four
 // values of it), for few rows and many parts (a decode step: 32 rows, tens to
-// hundreds of parts; a query encoding: hundreds of rows, tens of parts).  Thread (pg, dv) folds parts pg, pg + PG, ... of one
-// group, CH of them with all their loads issued together, so a merge waits
-// for one round trip to memory where CH * PG covers the parts; then the
-// groups are folded across lanes and, through LDS, across wavefronts.
+// hundreds of parts; a query encoding: hundreds of rows, tens of parts).
+// Thread (pg, dv) folds parts pg, pg + PG, ... of one group, CH of them with
+// all their loads issued together, so a merge waits for one round trip to
+// memory where CH * PG covers the parts; then the groups are folded across
+// lanes and, through LDS, across wavefronts.
 template <int DL, int THREADS>
 __global__ __launch_bounds__(THREADS) void lse_merge_wide_kernel(
     const float* __restrict__ o_parts, const float* __restrict__ lse_parts, int H, int Tq, int Hq,
@@ -180,34 +198,40 @@ __global__ __launch_bounds__(THREADS) void lse_merge_wide_kernel(
   const int64_t orow = ((int64_t)q * Hq + h) * d4;
   const f32x4* op = reinterpret_cast<const f32x4*>(o_parts) + z * (int64_t)H * (part_ostride / 4) +
                     orow + min(dv, d4 - 1);
-  float m = -INFINITY, sum = 0.f;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int p0 = pg; p0 < H; p0 += CH * PG) {
-    float l[CH];
-    f32x4 v[CH];
+  float m, sum;
+  f32x4 acc;
+  auto fold = [&](auto leave_out) {
+    m = -INFINITY, sum = 0.f;
+    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int p0 = pg; p0 < H; p0 += CH * PG) {
+      float l[CH];
+      f32x4 v[CH];
 #pragma unroll
-    for (int u = 0; u < CH; ++u) {
-      const int p = min(p0 + u * PG, H - 1);  // a part past the last weighs zero
-      l[u] = lp[p * part_lstride];
-      v[u] = op[p * (part_ostride / 4)];
+      for (int u = 0; u < CH; ++u) {
+        const int p = min(p0 + u * PG, H - 1);  // a part past the last weighs zero
+        l[u] = lp[p * part_lstride];
+        v[u] = op[p * (part_ostride / 4)];
+      }
+      float nm = m;
+#pragma unroll
+      for (int u = 0; u < CH; ++u)
+        if (p0 + u * PG < H) nm = fmaxf(nm, l[u]);
+      const float use = nm == -INFINITY ? 0.f : nm;  // no finite partial yet: weights 0
+      const float alpha = __expf(m - use);
+      sum *= alpha;
+      acc *= alpha;
+#pragma unroll
+      for (int u = 0; u < CH; ++u) {
+        const float w = p0 + u * PG < H ? __expf(l[u] - use) : 0.f;
+        sum += w;
+        if (decltype(leave_out)::value && (p0 + u * PG >= H || l[u] == -INFINITY)) continue;
+        acc += w * v[u];
+      }
+      m = nm;
     }
-    float nm = m;
-#pragma unroll
-    for (int u = 0; u < CH; ++u)
-      if (p0 + u * PG < H) nm = fmaxf(nm, l[u]);
-    const float use = nm == -INFINITY ? 0.f : nm;  // no finite partial yet: weights 0
-    const float alpha = __expf(m - use);
-    sum *= alpha;
-    acc *= alpha;
-#pragma unroll
-    for (int u = 0; u < CH; ++u) {
-      const bool has = p0 + u * PG < H && l[u] != -INFINITY;
-      const float w = has ? __expf(l[u] - use) : 0.f;
-      sum += w;
-      acc += w * (has ? v[u] : f32x4{0.f, 0.f, 0.f, 0.f});
-    }
-    m = nm;
-  }
+  };
+  fold(std::false_type{});
+  if (is_nan(acc)) fold(std::true_type{});  // as in the per-output kernel
   // lanes DL apart hold the same values' other parts
 #pragma unroll
   for (int off = DL; off < 64; off <<= 1) {
