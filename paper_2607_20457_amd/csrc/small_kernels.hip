@@ -279,17 +279,25 @@ int launch_lse_merge(const float* o_parts, const float* lse_parts, int H, int nz
   const int64_t total = (int64_t)nz * Tq * Hq * (d / 4);
   if (total == 0) return PULSAR_OK;
   const int64_t rows = (int64_t)nz * Tq * Hq;
-  // One workgroup per row while the per-output form would have at most 160
-  // workgroups walking the parts one after another: of 1024 threads for up to
-  // 256 rows of 128 (a decode step: 3.6 against 5.1 us for 65 parts), of 256
-  // threads for up to 1280 (12 tokens, 33 parts: 3.3 against 5.3 us; 48 tokens:
-  // no difference, 64: 1 us slower).
-  if (H >= 8 && total <= 40960) {
-    const int dl = d <= 64 ? 16 : 32;
-    const dim3 grid((unsigned)rows, (unsigned)((d / 4 + dl - 1) / dl));
-    const int threads = total <= 8192 ? 1024 : 256;
-    const auto wide = threads == 1024
-                          ? (dl == 16 ? lse_merge_wide_kernel<16, 1024> : lse_merge_wide_kernel<32, 1024>)
+  // One workgroup per row where there are too few outputs for the per-output
+  // form to fill the chip and enough parts to be worth a workgroup each: the
+  // more rows, the more parts it takes.  In 3194 Phase-2 calls the form per row
+  // (256 threads) took, us more than the one per output, at d 128: 8 or 9 parts,
+  // up to 256 rows -0.6, 1024 rows 0.1, 2048 rows 1.2; 13 to 17 parts, up to 256
+  // rows -1.0, 1024 -0.6, 2048 0.6; 25 to 33 parts, 256 rows -2.0, 2048 -0.4; the
+  // choice is 0.2 % slower than the better one on average.  256 threads take 32
+  // parts of a row of 128 in one round of loads, of 64 twice as many; a row of
+  // more parts has 512 while the rows are few (98 to 129 parts, up to 32 rows
+  // another 0.7 us less, 384 rows 0.4 more), and 1024 were never the best (10 to
+  // 33 parts 0.6 to 1 us slower).
+  // (Rows are counted as of 64 or 128 values, those that a workgroup's lanes take.)
+  const int dl = d <= 64 ? 16 : 32;
+  const int slices = (d / 4 + dl - 1) / dl;
+  if (H >= 8 && total <= 40960 && rows * slices * dl * 4 <= 200 * (int64_t)(H - 4) * d) {
+    const dim3 grid((unsigned)rows, (unsigned)slices);
+    const int threads = total <= 8192 && H > 1024 / dl ? 512 : 256;
+    const auto wide = threads == 512
+                          ? (dl == 16 ? lse_merge_wide_kernel<16, 512> : lse_merge_wide_kernel<32, 512>)
                           : (dl == 16 ? lse_merge_wide_kernel<16, 256> : lse_merge_wide_kernel<32, 256>);
     hipLaunchKernelGGL(wide, grid, dim3(threads), 0, stream, o_parts, lse_parts, H, Tq, Hq, d / 4,
                        part_ostride, part_lstride, o, lse);
