@@ -431,14 +431,15 @@ void attn_fwd_kernel(KernelArgs ka) {
   auto no_key = [&](int t) {
     return KSPLIT && tile_key(0) > min(row0 + t * 32 + l32, kv_end - 1);
   };
-  auto reset = [&]() {
+  auto reset = [&](auto exact_tag) {
 #pragma unroll
     for (int e = 0; e < DT; ++e)
 #pragma unroll
       for (int t = 0; t < QT; ++t) acc[e][t] = f32x16{};
 #pragma unroll
     for (int t = 0; t < QT; ++t) {
-      m_ref[t] = no_key(t) ? 0.f : -INFINITY;
+      // (the fast pass sets it in its first vector phase)
+      m_ref[t] = decltype(exact_tag)::value && no_key(t) ? 0.f : -INFINITY;
       l_run[t] = 0.f;
 #pragma unroll
       for (int j = 0; j < NSUM; ++j) lr_run[t][j] = 0.f;
@@ -552,7 +553,7 @@ void attn_fwd_kernel(KernelArgs ka) {
   // by more than 2^8, and O and the sums are rescaled.
   auto run_pass = [&](auto exact_tag) {
     constexpr bool EXACT = decltype(exact_tag)::value;
-    reset();
+    reset(exact_tag);
     if (EXACT) begin_pass();
 #pragma unroll
     for (int u = 0; u < 2; ++u)
