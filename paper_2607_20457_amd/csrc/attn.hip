@@ -93,15 +93,28 @@ int launch_attention(const AttnLaunch& a, hipStream_t stream) {
   // The key-split form, where a launch has no more items than compute units:
   // it then takes as long as its longest item, the last row tile over all
   // keys, which the split halves (and its workgroups load every tile for half
-  // as many rows).  Without / with it, launch and copy: 20 items of 1280 rows,
-  // 4 / 1 heads of 64 34.3 / 24.5 us; 50 of 1580 rows, 8 / 2 heads of 128 45.2
-  // / 32.0; 172 of 5445 rows, 4 / 1 of 64 110 / 67; 240 of 3803 rows, 16 / 8 of
-  // 64 82 / 77.  With more items the queue balances them: 384 of 2851 rows, 16
-  // / 16 of 64 88 / 101, 424 of 3380 rows, 32 / 8 of 128 120 / 150.
+  // as many rows).  Without / with it, us: 20 items of 1280 rows, 4 / 1 heads of
+  // 64 34.3 / 24.5; 128 of 512 rows (two sequences), 32 / 8 heads of 128 32.4 /
+  // 29.0; 256 of 4096 rows, 16 / 4 heads of 128 116 / 90; 256 of 2048 rows, 32 /
+  // 32 heads of 128 62.7 / 51.5.  With more items the queue balances them: 384 of
+  // 2851 rows, 16 / 16 heads of 64 88 / 101, 424 of 3380 rows, 32 / 8 of 128 120
+  // / 150.  So it does, over half a compute unit each, where items are short: a
+  // workgroup of several heads has 64 or 128 rows, and up to 2048 keys of them
+  // are split only while the halves fit the chip at once (160 items of 640 rows,
+  // 64 / 2 heads of 64 22.1 / 28.6; 192 of 1024 rows, 24 / 2 of 128, two sequences
+  // 39.5 / 42.2; 256 of 2048 rows, 32 / 8 of 128 67.9 / 71.7; 176 of 2816 rows, 16
+  // / 4 of 128 77.6 / 56.2), or are few for their length and read few KV heads
+  // (160 of 1280 rows, 32 / 2 of 128 43.9 / 38.2).  At d 64 a short row's tiles
+  // are not worth the merge (128 of 256 rows, 64 / 2 heads, two sequences 15.4 /
+  // 18.5).
   const int64_t items = (int64_t)ka.n_row_tiles * ka.hsub * a.Hkv * ka.nz;
+  const bool all = ka.heads_per_wg == 1 || a.n_kv > 2048 ||
+                   (a.d == 128 && a.Hkv * ka.nz <= 4 && items * 8 <= a.n_kv);
+  const int64_t most = all ? n_cu : ka.heads_per_wg == 4 && a.d == 64 && a.n_kv < 512 ? n_cu / 4
+                                                                                     : n_cu / 2;
   const int64_t split_lds = a.d == 128 ? attn_lds<128>(true, a.map.n_runs)
                                        : attn_lds<64>(true, a.map.n_runs);
-  ka.ksplit = a.causal && items <= n_cu && a.n_kv >= 256 && split_lds + 16 <= PULSAR_LDS_BYTES;
+  ka.ksplit = a.causal && items <= most && a.n_kv >= 256 && split_lds + 16 <= PULSAR_LDS_BYTES;
   if (ka.ksplit) {
     ka.rows_per_wg /= 2;
     ka.n_row_tiles = (a.n_q + ka.rows_per_wg - 1) / ka.rows_per_wg;
