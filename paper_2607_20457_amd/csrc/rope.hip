@@ -41,7 +41,7 @@ constexpr double kInvTwoPi = 0.15915494309189535;
 // 8 pairs), rotation by the angles of position p + p_add (ROTATE) or a plain
 // copy, 16-byte stores to dst.  `w_pair` and `p` may still be loading: the
 // first data is requested before they are used.  U: steps of heads whose loads
-// are in flight together (no more than the row has).  NT: the data passes the
+// are in flight together (no more than the row has).  NT: the loads pass the
 // caches by.
 template <int D, bool ROTATE, int U, bool NT>
 __device__ __forceinline__ void rope_row(const uint16_t* src, uint16_t* dst, int H, int64_t p,
@@ -114,15 +114,8 @@ __device__ __forceinline__ void rope_row(const uint16_t* src, uint16_t* dst, int
       if (hh < H) {
         u32x4 olo = clo[u], ohi = chi[u];
         if constexpr (ROTATE) rotate(clo[u], chi[u], olo, ohi);
-        u32x4* const d_lo = reinterpret_cast<u32x4*>(dst + (int64_t)hh * D);
-        u32x4* const d_hi = reinterpret_cast<u32x4*>(dst + (int64_t)hh * D + D / 2);
-        if constexpr (NT) {
-          __builtin_nontemporal_store(olo, d_lo);
-          __builtin_nontemporal_store(ohi, d_hi);
-        } else {
-          *d_lo = olo;
-          *d_hi = ohi;
-        }
+        *reinterpret_cast<u32x4*>(dst + (int64_t)hh * D) = olo;
+        *reinterpret_cast<u32x4*>(dst + (int64_t)hh * D + D / 2) = ohi;
       }
     }
   }
@@ -193,10 +186,11 @@ RopeKernel rope_for_heads(int H) {
          : steps <= 2 ? rope_kernel<D, HAS_POS, 2, NT>
                       : rope_kernel<D, HAS_POS, 4, NT>;
 }
-template <int D>
-RopeKernel rope_for(int H, bool has_pos, bool nt) {
-  return has_pos ? (nt ? rope_for_heads<D, true, true>(H) : rope_for_heads<D, true, false>(H))
-                 : (nt ? rope_for_heads<D, false, true>(H) : rope_for_heads<D, false, false>(H));
+template <bool HAS_POS>
+RopeKernel rope_for(int H, int d, bool nt) {
+  return d == 64 ? rope_for_heads<64, HAS_POS, false>(H)
+         : nt    ? rope_for_heads<128, HAS_POS, true>(H)
+                 : rope_for_heads<128, HAS_POS, false>(H);
 }
 
 // The table w_i: the caller's (checked finite) or base^(-2i/d).
@@ -256,14 +250,16 @@ int pulsar_rope(void* X, int batch, int64_t n_rows, int H, int d, const int32_t*
   const int64_t blocks = (rows + kRopeThreads / 64 - 1) / (kRopeThreads / 64);  // a wave per row
   if (blocks > 0x7fffffff) return PULSAR_EUNSUPPORTED;
   auto s = (hipStream_t)stream;
-  // Nontemporal accesses from 64 MB on.  A pass over data that comes from HBM
-  // is 10 to 12 % faster with them (256 MB 94.8 -> 86.1 us, 6.2 TB/s; 64 MB 25.8
-  // -> 22.7), one over data that the 256 MB last-level cache still holds is
-  // slower (64 MB 20.6 -> 22.0 us, 32 MB 8.4 -> 11.1): tensors of that size are
-  // mostly gone from it by the time a layer's rotation reads them.
-  const bool nt = rows * H * d * 2 >= (int64_t)64 << 20;
-  const RopeKernel kern = d == 128 ? rope_for<128>(H, pos != nullptr, nt)
-                                   : rope_for<64>(H, pos != nullptr, nt);
+  // Nontemporal loads from 256 MB on, the size of the last-level cache, for heads
+  // of 128.  Q and K together, plain / nontemporal, us, right after the projections
+  // that write them and (repeated) rotated over and over: 32768 tokens, 32 / 8
+  // heads (256 and 64 MB) 107.5 / 107.3, repeated 115.5 / 104.3; 32 / 32 heads (256
+  // MB each) 174 / 167, 188 / 186; 65536 tokens, 32 / 8 heads 221 / 209, 240 / 234.
+  // Smaller ones lose when repeated (128 MB 51.6 / 54.2), and at d 64 every load
+  // is half a cache line, which is then fetched twice (128 MB each 78 / 107).
+  // Nontemporal stores as well take longer after projections (256 and 64 MB 113.7).
+  const bool nt = rows * H * d * 2 >= (int64_t)256 << 20;
+  const RopeKernel kern = pos ? rope_for<true>(H, d, nt) : rope_for<false>(H, d, nt);
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kRopeThreads), 0, s, (uint16_t*)X, rows,
                      n_rows, H, pos, pos_offset, f);
   return hipGetLastError() == hipSuccess ? PULSAR_OK : PULSAR_EHIP;

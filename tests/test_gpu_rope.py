@@ -244,9 +244,8 @@ def test_contiguous_phase1_and_phase2_positions_end_to_end():
 @pytest.mark.parametrize("H,d", [(8, 128), (9, 128), (33, 128), (16, 64), (20, 64), (65, 64)])
 @pytest.mark.parametrize("posmode", ["rows", "array"])
 def test_rope_of_large_tensors_equals_its_halves(H, d, posmode):
-    # from 64 MB on the data passes the caches by; one, two and four steps of
-    # heads in flight, and more heads than that.  The halves are below the
-    # line, and below it the other tests compare with the oracle.
+    # one, two and four steps of heads in flight, and more heads than that, over
+    # many rows; the other tests compare smaller tensors with the oracle
     n = ((64 << 20) // (H * d * 2) + 2) // 2 * 2
     X = torch.randn((1, n, H, d), generator=torch.Generator("cuda").manual_seed(H), device="cuda",
                     dtype=torch.bfloat16)
@@ -254,6 +253,27 @@ def test_rope_of_large_tensors_equals_its_halves(H, d, posmode):
         torch.randint(0, 140000, (1, n), dtype=torch.int32, device="cuda")
     parts = [X[:, :n // 2].clone(), X[:, n // 2:].clone()]
     assert X.numel() * 2 >= 64 << 20 > parts[0].numel() * 2
+    P.rope_(X, pos)
+    for i, part in enumerate(parts):
+        if pos is None:
+            P.rope_(part, pos_offset=i * (n // 2))
+        else:
+            P.rope_(part, pos[:, i * (n // 2):(i + 1) * (n // 2)].contiguous())
+    assert torch.equal(X, torch.cat(parts, 1))
+
+
+@pytest.mark.parametrize("H", [8, 9, 33])
+@pytest.mark.parametrize("posmode", ["rows", "array"])
+def test_rope_of_256_mb_equals_its_halves(H, posmode):
+    # from 256 MB on (d 128) the loads pass the caches by; the halves are below
+    # that line.  One, two and more than four steps of heads.
+    n = ((256 << 20) // (H * 256) + 2) // 2 * 2
+    X = torch.randn((1, n, H, 128), generator=torch.Generator("cuda").manual_seed(40 + H),
+                    device="cuda", dtype=torch.bfloat16)
+    pos = None if posmode == "rows" else \
+        torch.randint(0, 140000, (1, n), dtype=torch.int32, device="cuda")
+    parts = [X[:, :n // 2].clone(), X[:, n // 2:].clone()]
+    assert X.numel() * 2 >= 256 << 20 > parts[0].numel() * 2
     P.rope_(X, pos)
     for i, part in enumerate(parts):
         if pos is None:
