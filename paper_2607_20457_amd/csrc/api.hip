@@ -155,7 +155,7 @@ int pulsar_chunk_summaries(const int32_t* ids, int batch, int64_t L, int num_blo
   const size_t need = pulsar_chunk_workspace_bytes(batch, L, num_blocks, chunk, vocab, scorer);
   if (need > 0 && workspace != nullptr) {
     if (workspace_bytes < need || !aligned16(workspace)) return PULSAR_EWORKSPACE;
-    if (scorer_split_pays(batch, L, num_blocks, vocab, scorer))
+    if (scorer_split_pays(batch, L, num_blocks, chunk, vocab, scorer))
       return launch_scorer_split(ids, batch, L, num_blocks, chunk, topk, vocab, scorer, sel_chunks,
                                  chunk_scores, workspace, (hipStream_t)stream);
   }

@@ -157,7 +157,7 @@ size_t maxidf_split_workspace(int batch, int64_t L, int num_blocks, int chunk, i
 // The one-workgroup Max-IDF kernels take these shapes with the ids held in
 // registers, and faster than the split path does.
 bool maxidf_one_wg_pays(int batch, int64_t L, int num_blocks, int chunk, int vocab);
-bool scorer_split_pays(int batch, int64_t L, int num_blocks, int vocab, int scorer);
+bool scorer_split_pays(int batch, int64_t L, int num_blocks, int chunk, int vocab, int scorer);
 int launch_maxidf_split(const int32_t* ids, int batch, int64_t L, int num_blocks, int chunk,
                         int topk, int vocab, int32_t* sel, int32_t* chunk_mindf, float* idf,
                         void* workspace, hipStream_t stream);

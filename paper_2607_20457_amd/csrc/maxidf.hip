@@ -118,7 +118,7 @@ static MaxidfPlan maxidf_plan(int64_t L, int num_blocks, int chunk, int vocab) {
 bool maxidf_one_wg_pays(int batch, int64_t L, int num_blocks, int chunk, int vocab) {
   const MaxidfPlan plan = maxidf_plan(L, num_blocks, chunk, vocab);
   return (plan.resident || plan.slots > 0) &&
-         !split_pays(PULSAR_SCORE_MAXIDF, batch, L, num_blocks, vocab);
+         !split_pays(kSplitMaxidf, PULSAR_SCORE_MAXIDF, batch, L, num_blocks, chunk, vocab);
 }
 
 size_t maxidf_lds_bytes(int64_t L, int num_blocks, int chunk, int vocab) {

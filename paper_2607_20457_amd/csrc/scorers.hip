@@ -526,8 +526,8 @@ size_t scorer_split_lds_bytes(int64_t L, int num_blocks, int chunk, int vocab, i
   return (size_t)split_score_layout(L, num_blocks, chunk, vocab, scorer).bytes;
 }
 
-bool scorer_split_pays(int batch, int64_t L, int num_blocks, int vocab, int scorer) {
-  return split_pays(scorer, batch, L, num_blocks, vocab);
+bool scorer_split_pays(int batch, int64_t L, int num_blocks, int chunk, int vocab, int scorer) {
+  return split_pays(kSplitScorer, scorer, batch, L, num_blocks, chunk, vocab);
 }
 
 int launch_scorer_split(const int32_t* ids, int batch, int64_t L, int num_blocks, int chunk,

@@ -20,26 +20,42 @@ __host__ __device__ inline int64_t split_seq_bytes(int num_blocks, int vocab) {
   return split_bits_bytes(num_blocks, vocab) + split_df_bytes(vocab);
 }
 
-// Whether the split path is the faster one for a batch that it takes, by
-// estimates in us that fit the times measured for both (1 to 16 sequences of
-// 4K to 128K ids, 4 to 16 blocks, vocabularies of 32000 and 128256) within
-// 20 %.  A workgroup that counts df over the whole sequence pays for its
-// blocks (a barrier and a round of table accesses each) and for its ids,
-// whatever the batch, and scores one block; the split path pays for three
-// launches, and per (sequence, block) for the vocabulary's tables.  The 3 us
-// are two more launches on the host.  Measured, one launch against split:
-//   Max-IDF, 1 x 8 x 2048 ids: 6.8 against 11.2 us; 1 x 16 x 8192: 20.8, 9.6
-//   BM25, 16 x 4 x 1024: 8.9, 16.3; 1 x 8 x 8192: 17.4, 14.8;
-//   16 x 16 x 8192: 29.5, 19.5
-inline bool split_pays(int scorer, int batch, int64_t L, int num_blocks, int vocab) {
-  const bool tf = scorer == PULSAR_SCORE_BM25 || scorer == PULSAR_SCORE_ENTROPY;
-  const bool maxidf = scorer == PULSAR_SCORE_MAXIDF;
-  const double kL = (double)L / 1024.0, grid = (double)batch * num_blocks;
-  const double one = maxidf ? 2.2 + 0.42 * num_blocks + 0.095 * kL
-                            : 5.0 + 0.30 * num_blocks + 0.11 * kL +
-                                  (tf ? 1.5 + 0.3 * kL / num_blocks : 0.0);
-  const double split = (maxidf ? 9.0 : tf ? 14.5 : 11.5) + (0.002 + 1.9e-7 * vocab) * grid;
-  return split + 3.0 < one;
+// Whether the split path is the faster one for a batch that it takes (1 to 16
+// sequences), by the time on the device.  A workgroup that counts df over the
+// whole sequence pays for its ids and its blocks, whatever the batch; the split
+// path pays for three launches, and per (sequence, block) for the vocabulary's
+// tables.  Measured over 3300 shapes of 1K to 256K ids, 2 to 16 blocks,
+// vocabularies of 2000 to 128256 and every scorer, by the slots of 4096 ids that
+// a sequence takes (summary.hpp):
+//   up to 8: one launch takes 0.42 to 1.02 times the split path's time;
+//   above 16: 0.96 to 2.6 times (its ids are packed, or streamed twice): BM25, 16
+//     x 8 x 10240 ids 43.6 against 38.7 us, Max-IDF 16 x 12 x 8192 20.2, 13.4;
+//   between: 0.58 to 1.5 times.  The difference, one launch less split, is linear
+//     in the tables' bytes, the ids, the blocks and their length, and in the
+//     rounds of 4096 ids that a workgroup scores: the split path's come in twos,
+//     and a round of BM25 or Entropy compares each id with its whole chunk.  One
+//     launch is chosen up to 1 us above the split path's time (the estimate is
+//     within 1.3 us over 3979 shapes, chunks of 16 to 256): a loop of calls, bound
+//     by two launches more, is then 2 to 3 us a call faster with it, a call by
+//     itself at most 1 us slower (1 x 10 x 4096 ids, in a loop 10.6 against 12.9 us,
+//     by itself 24.8 and 23.7, on the device 10.7 and 9.3).
+enum SplitKind { kSplitMaxidf, kSplitScorer };
+inline bool split_pays(SplitKind kind, int scorer, int batch, int64_t L, int num_blocks, int chunk,
+                       int vocab) {
+  const int64_t rounds = (L / num_blocks + 4095) / 4096, slots = num_blocks * rounds;
+  if (slots <= 8 || slots > 16) return slots > 16;
+  // us; per 1024 ids of a sequence, block, 1024 ids of a block, odd round, 64 ids of
+  // a chunk in it
+  struct { double c, ids, blocks, len, odd, cmp; } k;
+  if (kind == kSplitMaxidf) k = {-3.25, 0.064, 0.20, -0.065, -0.55, 0.0};
+  else if (scorer == PULSAR_SCORE_MAXIDF) k = {-3.55, 0.065, 0.17, 0.05, -0.55, 0.0};
+  else if (scorer == PULSAR_SCORE_TFIDF) k = {-4.6, 0.058, 0.28, 0.0, -1.0, 0.14};
+  else if (scorer == PULSAR_SCORE_BM25) k = {-3.85, 0.075, 0.154, -0.237, -0.57, -4.24};
+  else k = {-4.35, 0.069, 0.175, -0.10, 0.0, -4.57};
+  const double kL = (double)L / 1024.0;
+  double d = k.c + k.ids * kL + k.blocks * num_blocks + k.len * kL / num_blocks;
+  if (rounds & 1) d += k.odd + k.cmp * chunk / 64.0;
+  return d > 0.165e-6 * batch * num_blocks * vocab;
 }
 
 // Copy of n 16-byte units (K rounds of kSplitThreads, n > (K - 1) *

@@ -21,6 +21,15 @@ def f64(bits: np.ndarray) -> np.ndarray:
     return workload.bf16_bits_to_f32(bits).astype(np.float64)
 
 
+def poisoned_workspace(nbytes: int) -> torch.Tensor:
+    """A workspace whose contents tell afterwards whether a call has used it."""
+    return torch.full((nbytes,), 0xA5, dtype=torch.uint8, device="cuda")
+
+
+def was_used(workspace: torch.Tensor) -> bool:
+    return bool((workspace != 0xA5).any())
+
+
 # Acceptance: outputs max-abs 1e-2 and LSE max-abs 1e-3 (bf16 inputs, fp32
 # accumulation), plus a relative L2 bound of 1e-2 on O because at long
 # context |O| itself is of order 1e-2.

@@ -9,23 +9,22 @@ import torch
 import paper_2607_20457_amd as P
 from oracle import assembly, maxidf
 from paper_2607_20457_amd import workload
-from tests._helpers import gpu_available, to_dev_i32
+from tests._helpers import gpu_available, poisoned_workspace, to_dev_i32, was_used
 
 pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
 
 
 def _check(ids, N, m, k, V, idf_too=True, single=True):
-    """Both paths against the oracle: with the size query's workspace (split
-    over blocks and vocabulary where the shapes allow) and without one (one
-    workgroup per sequence).  Their outputs must also agree bit for bit."""
+    """Against the oracle, with the size query's workspace (which the call uses
+    where it splits the batch over blocks and vocabulary) and without one.
+    The outputs must also agree bit for bit."""
     sel_ref, mindf_ref, idf_ref, _ = maxidf.maxidf_summaries(ids, N, m, k, V)
     d_ids = to_dev_i32(ids)
     need = P.maxidf_workspace_bytes(ids.shape[0], ids.shape[1], N, m, V)
     outs = []
-    for ws in (("auto", None) if single else ("auto",)) if need else (None,):
-        print(f"maxidf parity: batch={ids.shape[0]} L={ids.shape[1]} N={N} m={m} k={k} V={V} "
-              f"path={'split' if ws else 'one workgroup per sequence'}", flush=True)
+    workspaces = [poisoned_workspace(need)] if need else []
+    for ws in workspaces + ([None] if single or not need else []):
         if idf_too:
             sel, mindf, idf = P.maxidf_summaries(d_ids, N, m, k, V, return_mindf=True,
                                                  return_idf=True, workspace=ws)
@@ -33,6 +32,10 @@ def _check(ids, N, m, k, V, idf_too=True, single=True):
             (sel, mindf), idf = P.maxidf_summaries(d_ids, N, m, k, V, return_mindf=True,
                                                    workspace=ws), None
         torch.cuda.synchronize()
+        used = ws is not None and was_used(ws)
+        print(f"maxidf parity: batch={ids.shape[0]} L={ids.shape[1]} N={N} m={m} k={k} V={V} "
+              f"path={'split' if used else 'workgroups of whole sequences'}", flush=True)
+        assert used or not (ws is not None and idf_too)  # the IDF table is the split path's
         assert np.array_equal(mindf.cpu().numpy(), mindf_ref)
         assert np.array_equal(sel.cpu().numpy(), sel_ref)
         if idf_too:
@@ -203,9 +206,11 @@ def test_batch_beyond_compute_units(L, N, batch, m):
     (32 * 1024, 32, 16, 32000, "compact bitmaps (N > 16)"),
     (64 * 2048, 64, 32, 128256, "compact bitmaps, 64 blocks"),
     (20 * 1024, 20, 32, 140000, "general bitmaps (vocab > 131072)"),
-    (3 * 8192, 3, 32, 128256, "stamp code, streaming (3 rounds)"),
-    (12 * 4096, 12, 16, 50000, "stamp code, streaming (blocks of 4096)"),
+    (3 * 8192, 3, 32, 128256, "stamp code, slots (2 per block)"),
+    (12 * 4096, 12, 16, 50000, "stamp code, slots (one per block)"),
     (2 * 8192, 2, 8, 1000, "stamp code, resident (2 rounds)"),
+    (3 * 50000, 3, 16, 5000, "stamp code, streaming (7 rounds a block, the last ragged)"),
+    (5 * 36864, 5, 32, 128256, "stamp code, streaming (5 rounds a block, the last half full)"),
 ])
 def test_every_kernel_layout(L, N, m, V, layout):
     # one case per df-counting layout the host plan can pick
@@ -223,7 +228,7 @@ def test_every_kernel_layout(L, N, m, V, layout):
     (40960, 5, 128, 145000, 1),     # a large presence table
     (4096, 2, 16, 1, 1),            # one id in the vocabulary: every df = N
     (24576, 24, 16, 32000, 3),      # 24 blocks: df bytes (more than 16 blocks), held in LDS
-    (26000, 2, 8, 5000, 2),         # blocks of 13000 ids: two rounds of loads, the second partial
+    (26000, 2, 8, 5000, 2),         # blocks of 13000 ids: a partial round of loads
 ])
 def test_split_path_shapes(L, N, m, V, batch):
     ids = np.stack([workload.zipf_ids(6000 + b + m, L, V) for b in range(min(batch, 4))])
@@ -305,3 +310,26 @@ def test_slot_ids_outside_the_vocabulary_stay_in_the_table():
         ids[1] = 2 ** 31 - 1
         sel = P.maxidf_summaries(ids, 4, 32, 3, V, workspace=None)
         assert sel.shape == (2, 4, 3) and int(sel.min()) >= 0 and int(sel.max()) < 128
+
+
+@pytest.mark.parametrize("b,L,N,idf,split", [
+    # above 16 slots of 4096 ids: split, also where an estimate by the ids alone
+    # had one launch, up to twice as slow
+    (16, 12 * 8192, 12, False, True),
+    (8, 8 * 10240, 8, False, True),
+    (1, 12 * 5120, 12, False, True),
+    # up to 8: one launch, unless the IDF table is wanted
+    (1, 8 * 2048, 8, False, False),
+    (16, 4 * 4096, 4, False, False),
+    (1, 8 * 2048, 8, True, True),
+    # between: by the vocabulary's tables and the ids
+    (1, 16 * 4096, 16, False, True),
+    (16, 16 * 2048, 16, False, False),
+])
+def test_which_batches_are_split(b, L, N, idf, split):
+    V = 128256
+    ids = torch.randint(0, V, (b, L), dtype=torch.int32, device="cuda")
+    ws = poisoned_workspace(P.maxidf_workspace_bytes(b, L, N, 32, V))
+    P.maxidf_summaries(ids, N, 32, 4, V, return_idf=idf, workspace=ws)
+    torch.cuda.synchronize()
+    assert was_used(ws) == split
