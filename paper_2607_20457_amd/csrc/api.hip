@@ -287,8 +287,7 @@ static int attn_splits(int n_shards, int Tq, int64_t S, int Hq, int Hkv) {
 
 static int phase2_splits(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d) {
   if (S <= 0) return 1;
-  if (decode_applies(Tq, Hq, Hkv, d))
-    return decode_parts(n_shards, S, Hkv, decode_min_keys(Tq * (Hq / Hkv)));
+  if (decode_applies(Tq, Hq, Hkv, d)) return decode_shard_parts(n_shards, Tq, S, Hq, Hkv, d, false);
   if (packed_applies(Tq, Hq, Hkv, d)) return packed_parts(n_shards, S, Hkv);
   return attn_splits(n_shards, Tq, S, Hq, Hkv);
 }
@@ -465,16 +464,18 @@ QueryPlan query_plan(int n_shards, int Tq, int64_t S, int64_t G, int Hq, int Hkv
   p.gen_decode = p.decode || ((d == 64 || d == 128) && Hq / Hkv <= 32 && G + Tq <= kGenDecodeRows &&
                                (int64_t)Tq * (Hq / Hkv) <= kGenDecodeQueryRows);
   if (p.decode) {
+    p.np_shard = min_keys == kDecodeMinKeys
+                     ? decode_shard_parts(n_shards, Tq, S, Hq, Hkv, d, true)
+                     : decode_parts(n_shards, S, Hkv, min_keys);
     min_keys = std::max(min_keys, decode_min_keys(Tq * (Hq / Hkv)));
-    p.np_shard = decode_parts(n_shards, S, Hkv, min_keys);
   } else {
-    p.np_shard = n_shards > 0 ? phase2_splits(n_shards, Tq, S, Hq, Hkv, d) : 0;
+    p.np_shard = n_shards > 0 ? attn_splits(n_shards, Tq, S, Hq, Hkv) : 0;
   }
   if (p.gen_decode) {
     p.np_gen = decode_parts(1, G + Tq, Hkv, gen_min_keys(Tq * (Hq / Hkv), G + Tq, min_keys));
     p.parts = n_shards * p.np_shard + p.np_gen;
   } else {
-    p.np_gen = G > 0 ? phase2_splits(1, Tq, G, Hq, Hkv, d) : 0;
+    p.np_gen = G > 0 ? attn_splits(1, Tq, G, Hq, Hkv) : 0;
     p.parts = n_shards * p.np_shard + p.np_gen + 1;
   }
   return p;

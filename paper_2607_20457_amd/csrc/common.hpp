@@ -168,6 +168,7 @@ int decode_parts(int n_shards, int64_t S, int Hkv, int min_keys);
 int decode_waves(int n_shards, int64_t S, int Hkv, int min_keys);
 int decode_ranges(int64_t S, int nparts);
 int decode_min_keys(int query_rows);  // least keys per range worth a partial of the rows
+int decode_shard_parts(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d, bool merges);
 // The most ranges, of all shards, for up to n_shards shards of up to S keys (the
 // count itself drops where a range's length goes up to the next whole step).
 int64_t decode_ranges_most(int n_shards, int64_t S, int Hkv, int min_keys);

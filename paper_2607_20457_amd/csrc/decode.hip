@@ -335,11 +335,11 @@ int decode_part_len(int64_t S, int nparts) {
 // Key ranges per shard for the decode kernel: enough waves for one
 // four-wave workgroup per compute unit (as fast as two per compute unit,
 // measured, with half the partials to merge), at least min_keys keys per
-// range.  With min_keys = kDecodeMinKeys (one step) a short context is cut
-// until the waves suffice or each has one step: such a call is bound by the
-// chain of dependent steps in a wave, not by bytes (one token over 4 x 1021
-// keys of 8 KV heads, d 128, with at least 256 / 128 / 64 / 32 keys per
-// range: 17.5 / 14.0 / 11.5 / 10.6 us for the launch and the merge).
+// range.  A short context is bound by the chain of dependent steps in a wave,
+// not by bytes: with min_keys = kDecodeMinKeys (one step) it is cut until the
+// waves suffice or each has one step (one token over 4 x 1021 keys of 8 KV heads,
+// d 128, with at least 256 / 128 / 64 / 32 keys per range: 17.5 / 14.0 / 11.5 /
+// 10.6 us for the launch and the merge).
 int decode_parts(int n_shards, int64_t S, int Hkv, int min_keys) {
   if (S <= 0 || n_shards <= 0 || Hkv <= 0) return 1;
   return decode_ranges(S, decode_waves(n_shards, S, Hkv, min_keys));
@@ -360,12 +360,31 @@ int decode_ranges(int64_t S, int nparts) {
 }
 
 // A range is to be worth its partial: the more query rows a KV head has, the
-// more bytes that is.  About four keys a row (launch and merge, 4 x 1000 keys of 8 KV
-// heads and 4 heads each, ranges of 32 keys / of four a row: 8 tokens 20.0 / 14.9
-// us, 4 tokens 13.4 / 12.4; 8 tokens with ranges of 256 keys 18.5), in powers
-// of two: fewer tokens then never take more bytes of partials.
+// more bytes that is, so about four keys a row, in powers of two: fewer tokens
+// then never take more bytes of partials.
 int decode_min_keys(int query_rows) {
   return query_rows <= 8 ? kDecodeMinKeys : query_rows <= 16 ? 2 * kDecodeMinKeys : 4 * kDecodeMinKeys;
+}
+
+// Key ranges per shard of a call: these short ones where the steps that they
+// take off a wave's chain are worth what their partials cost over ranges of 256
+// keys, else the latter.  A step is worth about 0.85 us (d 64: 0.6) and a MB of
+// partials costs 0.5 us, written and merged; over shards of one long range the
+// merge itself is another launch unless the call has one anyway (2.5 us, and 4.5
+// against the short chain of fewer than four waves).  Launches and merge, long /
+// short ranges, us: one token over 4 x 1000 keys of 8 KV heads, d 128, 16.9 /
+// 10.0, over 64 x 100 9.6 / 10.9; 8 tokens of 4 heads each over 4 x 1000 keys
+// 17.4 / 14.7, over 4 x 4096 20.6 / 21.4; 4 tokens over 32 x 300 15.6 / 17.7;
+// one token over 100 keys of one KV head, d 64, 4.6 / 5.7.  Over 575 shapes the
+// choice is at most 6 % slower than ranges of 256 keys and 12 % faster on average.
+int decode_shard_parts(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d, bool merges) {
+  const int few = decode_parts(n_shards, S, Hkv, kDecodeMinKeysScarce);
+  const int many = decode_parts(n_shards, S, Hkv, decode_min_keys(Tq * (Hq / Hkv)));
+  if (few >= many || S <= 0) return few;
+  const int steps = (decode_part_len(S, few) - decode_part_len(S, many)) / DEC_KEYS;
+  const double mb = 1e-6 * n_shards * (many - few) * Tq * Hq * (d + 1) * 4;
+  const double launch = few > 1 || merges ? 0.0 : (int64_t)n_shards * Hkv < 4 ? 4.5 : 2.5;
+  return steps * (d == 64 ? 0.6 : 0.85) > 0.5 * mb + launch ? many : few;
 }
 
 int64_t decode_ranges_most(int n_shards, int64_t S, int Hkv, int min_keys) {

@@ -210,6 +210,21 @@ def test_phase2_sizes_of_nothing():
         assert lib.pulsar_phase2_query_workspace_bytes(n, 0, 8192, 10, 32, 8, 128) == 0
 
 
+@pytest.mark.parametrize("n,Tq,S,Hq,Hkv,d,ranges", [
+    # decode kernel: the shards' ranges of 256 keys (one: no workspace) where
+    # shorter ones would not pay for their partials and the merge launch
+    (64, 1, 100, 32, 8, 128, 1), (1, 4, 100, 32, 8, 128, 1), (1, 1, 100, 8, 2, 128, 1),
+    (64, 4, 100, 4, 1, 64, 1), (32, 4, 300, 32, 8, 128, 2), (4, 8, 4096, 32, 8, 128, 16),
+    (1, 8, 256, 8, 2, 128, 1),
+    # and the shorter ones where they do
+    (4, 1, 1021, 32, 8, 128, 32), (1, 1, 200, 32, 8, 128, 7), (4, 8, 1000, 32, 8, 128, 8),
+])
+def test_phase2_partial_ranges(n, Tq, S, Hq, Hkv, d, ranges):
+    # the key ranges per shard that a call is cut into, from its workspace size
+    need = n * ranges * Tq * Hq * (d + 1) * 4 if ranges > 1 else 0
+    assert _lib.lib().pulsar_phase2_workspace_bytes(n, Tq, S, Hq, Hkv, d) == need
+
+
 @pytest.mark.parametrize("Hq,Hkv,d", [(32, 8, 128), (8, 2, 128), (4, 1, 64), (16, 16, 64),
                                       (16, 8, 64), (64, 8, 128), (128, 2, 64)])
 def test_phase2_query_size_never_drops(Hq, Hkv, d):

@@ -132,7 +132,9 @@ def test_phase2_far_larger_later_score():
     (8, 1, 4100, 8, 2, 64),     # group 4, 32 packed rows, many key ranges
     (3, 4, 777, 8, 8, 128),     # group 1
     (1, 4, 1021, 32, 8, 128),   # one 32-key step per range, the last of 29 keys
-    (1, 1, 64, 4, 1, 64),       # two ranges of one step
+    (1, 4, 161, 8, 2, 128),     # six ranges of one step, the last of one key
+    (1, 1, 64, 4, 1, 64),       # one range of two steps: a merge would cost more
+    (4, 32, 300, 32, 8, 128),   # ranges of 256 keys: shorter ones' partials would cost more
     (1, 2, 8225, 4, 1, 128),    # 256 ranges asked for, of 64 keys each after rounding
 ])
 def test_decode_kernel_shapes(Tq, H, S, Hq, Hkv, d):
