@@ -285,10 +285,28 @@ static int attn_splits(int n_shards, int Tq, int64_t S, int Hq, int Hkv) {
   return (int)ns;
 }
 
+// Whether the packed kernel takes a call of pulsar_phase2_partial.  Five and six
+// tiles (d 64) are only faster than the attention kernel over longer shards, and
+// where that kernel's 64-row tiles hold few rows (more than 4 heads per KV head),
+// or its workgroups are few or just more than the chip takes at once.  Attention
+// / packed, us: 5 tiles, 16 / 4 heads, 32 x 300 keys 12.9 / 14.8, 8 x 4096 23.3 /
+// 23.9, 1 x 500 (4 workgroups) 15.3 / 11.9, 4 x 1000 (32) 18.6 / 14.8; 32 / 2
+// heads, 16 x 500 14.3 / 15.3, 8 x 4096 27.7 / 19.6; 16 / 16 heads, 5 x 3000 (320
+// workgroups) 44.6 / 32.0.
+static bool packed_partial(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d) {
+  if (decode_applies(Tq, Hq, Hkv, d) || !packed_applies(Tq, Hq, Hkv, d)) return false;
+  const int group = Hq / Hkv, rows = attn_rows_per_wg(group, false);
+  if (packed_tiles(Tq, group) <= 4) return true;
+  const int64_t wgs = (int64_t)n_shards * attn_splits(n_shards, Tq, S, Hq, Hkv) * Hkv *
+                      (group / std::min(group, 4)) * ((Tq + rows - 1) / rows);
+  return S > 384 && (wgs < 64 || (S > 512 && (group > 4 || wgs > 256)));
+}
+
 static int phase2_splits(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d) {
   if (S <= 0) return 1;
   if (decode_applies(Tq, Hq, Hkv, d)) return decode_shard_parts(n_shards, Tq, S, Hq, Hkv, d, false);
-  if (packed_applies(Tq, Hq, Hkv, d)) return packed_parts(n_shards, S, Hkv);
+  if (packed_partial(n_shards, Tq, S, Hq, Hkv, d))
+    return packed_shard_parts(n_shards, Tq, S, Hq, Hkv, d);
   return attn_splits(n_shards, Tq, S, Hq, Hkv);
 }
 
@@ -329,7 +347,7 @@ int pulsar_phase2_partial(const void* q, const void* K, const void* V, int n_sha
   if (!aligned16(q) || (S > 0 && (!aligned16(K) || !aligned16(V))) || !aligned16(o_parts))
     return PULSAR_EINVAL;
   const bool decode = decode_applies(Tq, Hq, Hkv, d);
-  const bool packed = !decode && packed_applies(Tq, Hq, Hkv, d);
+  const bool packed = packed_partial(n_shards, Tq, S, Hq, Hkv, d);
   // The key ranges that the call prefers, or else the fewer ones of a workspace
   // sized for other shapes (none where that is one range per shard).
   int ns = phase2_splits(n_shards, Tq, S, Hq, Hkv, d);

@@ -195,6 +195,8 @@ constexpr int kPackedMinKeysScarce = 512;  // where partials have to be few
 bool packed_applies(int Tq, int Hq, int Hkv, int d);
 int packed_parts(int n_shards, int64_t S, int Hkv, int min_keys = kPackedMinKeys);
 int packed_ranges(int64_t S, int nparts);
+int packed_shard_parts(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d);
+int packed_tiles(int Tq, int group);  // row tiles of a KV head
 int64_t packed_ranges_most(int n_shards, int64_t S, int Hkv, int min_keys = kPackedMinKeys);
 // Tokens that a packed launch takes at most.
 int packed_tokens(int Hq, int Hkv, int d);

@@ -29,6 +29,7 @@
 // sums rescaled, as the scores grow.  P enters PV rounded to bf16, O is
 // divided by the sum of those rounded weights, the LSE uses the fp32 sum.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "common.hpp"
@@ -542,12 +543,6 @@ void packed_attn_kernel(PackedArgs a) {
   }
 }
 
-// Row tiles of a KV head.
-int packed_tiles(int Tq, int group) {
-  const int tokens = 32 / group;
-  return (Tq + tokens - 1) / tokens;
-}
-
 template <int D, int RT, int NG>
 int launch_packed_impl(const PackedArgs& a, int64_t nwg, hipStream_t stream) {
   constexpr int lds = PkLds<D, RT, NG>::BYTES;
@@ -616,6 +611,33 @@ int packed_parts(int n_shards, int64_t S, int Hkv, int min_keys) {
 int packed_ranges(int64_t S, int nparts) {
   const int64_t len = packed_part_len(S, nparts);
   return (int)((S + len - 1) / len);
+}
+
+// Row tiles of a KV head.
+int packed_tiles(int Tq, int group) {
+  const int tokens = 32 / group;
+  return (Tq + tokens - 1) / tokens;
+}
+
+// Key ranges per shard of a call that merges them in a launch of its own: the
+// number with the least of a workgroup's steps, the launch (2.7 us) and the
+// partials' bytes (0.63 us a MB, written and merged), or one.  128 keys take
+// 0.86, 1.6 and 2.2 us for up to two, four and six tiles at d 64, 1.4 and 2.5 us
+// for up to two and four at d 128 (fitted to 3400 times of 612 shapes with up to
+// 64 ranges, within 3 % on average).  16 tokens of 4 heads over 32 x 300 keys, 4
+// KV heads of 64: 8.1 us in one range a shard, 11.8 in two; over 5 x 3000 keys
+// 24.3 in one, 13.3 in eight.
+int packed_shard_parts(int n_shards, int Tq, int64_t S, int Hq, int Hkv, int d) {
+  const int most = packed_parts(n_shards, S, Hkv);
+  if (most == 1) return 1;
+  constexpr int unit = PK_KEYS * PK_WAVES;
+  const int tiles = packed_tiles(Tq, Hq / Hkv);
+  const double step = d == 64 ? (tiles <= 2 ? 0.86 : tiles <= 4 ? 1.6 : 2.2) : tiles <= 2 ? 1.4 : 2.5;
+  const double mb = 0.63e-6 * n_shards * Tq * Hq * (d + 1) * 4;  // of one range a shard, in us
+  const double best = std::sqrt(step * (double)S / unit / mb);
+  const int np = packed_ranges(S, (int)std::min<double>(std::max(best + 0.5, 2.0), most));
+  const auto steps = [&](int parts) { return step * packed_part_len(S, parts) / unit; };
+  return steps(np) + 2.7 + mb * np < steps(1) ? np : 1;
 }
 
 int64_t packed_ranges_most(int n_shards, int64_t S, int Hkv, int min_keys) {

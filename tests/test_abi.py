@@ -218,6 +218,11 @@ def test_phase2_sizes_of_nothing():
     (1, 8, 256, 8, 2, 128, 1),
     # and the shorter ones where they do
     (4, 1, 1021, 32, 8, 128, 32), (1, 1, 200, 32, 8, 128, 7), (4, 8, 1000, 32, 8, 128, 8),
+    # packed kernel: likewise
+    (32, 16, 300, 16, 4, 64, 1), (32, 24, 300, 16, 4, 64, 1), (16, 16, 200, 16, 4, 64, 1),
+    (5, 16, 3000, 16, 4, 64, 8),
+    # five tiles of short shards: the attention kernel, one range
+    (32, 40, 300, 16, 4, 64, 1), (32, 10, 300, 32, 2, 64, 1),
 ])
 def test_phase2_partial_ranges(n, Tq, S, Hq, Hkv, d, ranges):
     # the key ranges per shard that a call is cut into, from its workspace size
