@@ -55,7 +55,7 @@
 #pragma once
 #include <type_traits>
 
-#include "common.hpp"
+#include "tiles.hpp"
 
 namespace pulsar_attn {
 
@@ -89,16 +89,6 @@ using pulsar_attn::KernelArgs;
 
 constexpr int BN = 64;          // keys per tile
 constexpr float MAX_SLACK = 8.0f;  // exact pass: log2 slack before the running max is raised
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-constexpr int kBufferFlags = 0x00020000;  // raw 32-bit buffer access (word 3 of the resource)
-__device__ constexpr bf16x2 kOnes2 = {(__bf16)1.0f, (__bf16)1.0f};
-
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
-typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-
 template <int D>
 struct Tile {
   static constexpr int CPR = D / 8;               // 16-byte data chunks per row
@@ -113,26 +103,6 @@ struct Tile {
   static constexpr int GROUP = 2 * K_BYTES + 2 * V_BYTES;
   static constexpr int LDS_SPLIT = 2 * GROUP + 6 * BN * 4;
 };
-
-
-
-// One 16-byte-per-lane buffer load that writes LDS directly: lane l's 16
-// bytes land at LDS byte lds_base + 16*l.  Issued from asm so that the
-// compiler does not order the key loop's LDS reads after it (it cannot tell
-// that they read the other stage); the loop waits for it explicitly
-// (vmcnt) before the barrier that publishes the stage.
-__device__ __forceinline__ void lds_dma16(__amdgpu_buffer_rsrc_t rsrc, uint32_t voffset,
-                                          uint32_t lds_base) {
-  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds"
-               :
-               : "v"(voffset), "s"(rsrc), "{m0}"(lds_base)
-               : "memory");
-}
-
-__device__ __forceinline__ int swap_bits23(int r) {
-  return (r & ~12) | ((r >> 1) & 4) | ((r << 1) & 8);
-}
-
 // Matrix-phase fragment reads run this many matrix steps ahead.
 constexpr int MDEPTH = 4;
 
@@ -268,7 +238,7 @@ void attn_fwd_kernel(KernelArgs ka) {
   // V: the four group-0 waves move the V tile straight into LDS as well,
   //   keys as rows (2D bytes each): wave w issues segments w, w+4, ...; lane
   //   l of segment sg fills chunk position (64 sg + l) % CPR of row
-  //   (64 sg + l) / CPR, which holds 16-byte chunk position ^ vswz(row) of
+  //   (64 sg + l) / CPR, which holds 16-byte chunk position ^ v_swizzle(row) of
   //   that key.  The PV product reads V^T fragments from it with transposing
   //   reads (v_frag); the chunk swizzle puts the four rows that one 16-lane
   //   group of such a read touches in disjoint banks.  A key past the end
@@ -329,7 +299,6 @@ void attn_fwd_kernel(KernelArgs ka) {
     }
   };
   constexpr int NVSEG = T::V_SEGS / 4;  // V segments per group-0 wave
-  auto vswz = [](int r) { return (4 * ((r * T::CPR) / 16)) % T::CPR; };
   int vdma_row[NVSEG];
   uint32_t vdma_col[NVSEG];
 #pragma unroll
@@ -337,7 +306,7 @@ void attn_fwd_kernel(KernelArgs ka) {
     const int slot = (wk + 4 * i) * 64 + lane;
     const int r = (slot / T::CPR) & (BN - 1);
     vdma_row[i] = r;
-    vdma_col[i] = head_off + (uint32_t)((slot % T::CPR) ^ vswz(r)) * 16;
+    vdma_col[i] = head_off + (uint32_t)((slot % T::CPR) ^ v_swizzle<D>(r)) * 16;
   }
   auto issue_v = [&](int tile, lds_u8* st) {
     const uint32_t st_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)st);
@@ -355,27 +324,11 @@ void attn_fwd_kernel(KernelArgs ka) {
     return *reinterpret_cast<const lds_bf16x8*>(sK + (u * 32 + l32) * T::K_STRIDE +
                                                 (16 * s + 8 * g) * 2);
   };
-  // V^T rows e*32.., keys u*32+16c.. of the tile, as the A operand of PV,
-  // from the raw V tile with two transposing reads.  Within each 16-lane
-  // group such a read hands lane i, for slot j, element i%4 of the four that
-  // lane 4j + i/4 addressed; so lane 16a + 4j + q addresses key row
-  // 8(a/2) + j (+4 for the second read) at head_dim 16(a%2) + 4q, and lane
-  // 16a + i receives head_dim 16(a%2) + i of keys 8(a/2) .. +7.
+  // V^T rows e*32.., keys u*32+16c.. of the tile, as the A operand of PV
   uint32_t vtr_base[DT];
-  {
-    const int a16 = lane >> 4, j = (lane >> 2) & 3, q = lane & 3;
-    const int trow = 8 * (a16 >> 1) + j;  // vswz of every row read equals vswz(trow)
-    const int cb = 2 * (a16 & 1) + (q >> 1);
-#pragma unroll
-    for (int e = 0; e < DT; ++e)
-      vtr_base[e] = trow * (2 * D) + 16 * ((4 * e + cb) ^ vswz(trow)) + 8 * (q & 1);
-  }
+  v_tr_base<D>(lane, vtr_base);
   auto v_frag = [&](const lds_u8* sV, int u, int c, int e) -> bf16x8 {
-    const lds_u8* b = sV + vtr_base[e] + (u * 32 + 16 * c) * (2 * D);
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)b);
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(b + 4 * (2 * D)));
-    return __builtin_bit_cast(bf16x8,
-                              (s16x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+    return v_tr_read<D>(sV + vtr_base[e] + (u * 32 + 16 * c) * (2 * D));
   };
 
 

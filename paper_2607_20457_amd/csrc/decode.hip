@@ -33,33 +33,12 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "common.hpp"
+#include "tiles.hpp"
 
 namespace {
 
 constexpr int DEC_WAVES = 4;
 constexpr int DEC_KEYS = 32;  // keys per step
-constexpr int kDecBufferFlags = 0x00020000;  // raw 32-bit buffer access (word 3 of the resource)
-
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-__device__ constexpr bf16x2 kOnes2 = {(__bf16)1.0f, (__bf16)1.0f};
-
-// 16 bytes per lane from global memory straight into LDS at lds_base + 16*l.
-__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t rsrc, uint32_t voffset,
-                                      uint32_t lds_base) {
-  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds"
-               :
-               : "v"(voffset), "s"(rsrc), "{m0}"(lds_base)
-               : "memory");
-}
-
-__device__ __forceinline__ int swap23(int r) {
-  return (r & ~12) | ((r >> 1) & 4) | ((r << 1) & 8);
-}
 
 struct DecodeArgs {
   const uint16_t* Q;  // bf16 [Tq, Hq, D]
@@ -146,9 +125,9 @@ void decode_attn_kernel(DecodeArgs a) {
   const uint32_t row_bytes = (uint32_t)(a.Hkv * D * 2);
   const uint32_t head_off = (uint32_t)(kvh * D * 2);
   const __amdgpu_buffer_rsrc_t k_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(Kz), (short)0, (int)(zstride * 2), kDecBufferFlags);
+      const_cast<uint16_t*>(Kz), (short)0, (int)(zstride * 2), kBufferFlags);
   const __amdgpu_buffer_rsrc_t v_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(Vz), (short)0, (int)(zstride * 2), kDecBufferFlags);
+      const_cast<uint16_t*>(Vz), (short)0, (int)(zstride * 2), kBufferFlags);
 
   // ---- Q fragments (B operand): column l32 = packed row (token, head) ----
   bf16x8 qf[DS];
@@ -166,10 +145,10 @@ void decode_attn_kernel(DecodeArgs a) {
   }
 
   // ---- loads of one step ----------------------------------------------------
-  // K: lane (l32, g) loads key swap23(l32) of the step, 16-byte chunks
+  // K: lane (l32, g) loads key swap_bits23(l32) of the step, 16-byte chunks
   // 2s + g.  A key past the end reads the range's first key (finite; masked).
   auto load_k = [&](int j, bf16x8 (&kf)[DS]) {
-    int key = kv_begin + j * DEC_KEYS + swap23(l32);
+    int key = kv_begin + j * DEC_KEYS + swap_bits23(l32);
     key = key < kv_end ? key : kv_begin;
     const uint32_t base = (uint32_t)key * row_bytes + head_off + 16u * g;
 #pragma unroll
@@ -180,8 +159,7 @@ void decode_attn_kernel(DecodeArgs a) {
   };
   // V: keys as rows of 2D bytes in the wave's LDS stage; lane l of segment
   // sg fills chunk position (64 sg + l) % CPR of row (64 sg + l) / CPR with
-  // chunk position ^ vswz(row) of that key's row.
-  auto vswz = [](int r) { return (4 * ((r * CPR) / 16)) % CPR; };
+  // chunk position ^ v_swizzle(row) of that key's row.
   lds_u8* const wave_lds = (lds_u8*)smem + wave * 2 * V_BYTES;
   auto issue_v = [&](int j, int stage) {
     const uint32_t st = __builtin_amdgcn_readfirstlane(
@@ -192,29 +170,17 @@ void decode_attn_kernel(DecodeArgs a) {
       const int r = slot / CPR;
       int key = kv_begin + j * DEC_KEYS + r;
       key = key < kv_end ? key : kv_begin;
-      dma16(v_rsrc, (uint32_t)key * row_bytes + head_off + (uint32_t)((slot % CPR) ^ vswz(r)) * 16u,
-            st + sg * 1024);
+      lds_dma16(v_rsrc, (uint32_t)key * row_bytes + head_off +
+                            (uint32_t)((slot % CPR) ^ v_swizzle<D>(r)) * 16u,
+                st + sg * 1024);
     }
   };
-  // V^T fragment (rows e*32.., keys 16c..16c+15) by two transposing reads:
-  // lane 16a + 4j + q addresses key row 8(a/2) + j (+4) at head_dim
-  // 16(a%2) + 4q; lane 16a + i receives head_dim 16(a%2) + i of keys
-  // 8(a/2) .. +7, the k-slots that P's B layout puts in lane a's half.
+  // V^T fragment (rows e*32.., keys 16c..16c+15), whose k-slots are those that
+  // P's B layout holds
   uint32_t vtr_base[DT];
-  {
-    const int a16 = lane >> 4, jj = (lane >> 2) & 3, q = lane & 3;
-    const int trow = 8 * (a16 >> 1) + jj;
-    const int cb = 2 * (a16 & 1) + (q >> 1);
-#pragma unroll
-    for (int e = 0; e < DT; ++e)
-      vtr_base[e] = trow * (2 * D) + 16 * ((4 * e + cb) ^ vswz(trow)) + 8 * (q & 1);
-  }
+  v_tr_base<D>(lane, vtr_base);
   auto v_frag = [&](const lds_u8* sV, int c, int e) -> bf16x8 {
-    const lds_u8* b = sV + vtr_base[e] + (16 * c) * (2 * D);
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)b);
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(b + 4 * (2 * D)));
-    return __builtin_bit_cast(bf16x8,
-                              (s16x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+    return v_tr_read<D>(sV + vtr_base[e] + (16 * c) * (2 * D));
   };
 
   f32x16 acc[DT];
@@ -235,7 +201,7 @@ void decode_attn_kernel(DecodeArgs a) {
   auto step = [&](int j, auto kb_tag) {
     constexpr int KB = decltype(kb_tag)::value;
     const bool v1 = j + 1 < nsteps;
-    // S^T of this step: row i = key swap23(i), column = packed query row
+    // S^T of this step: row i = key swap_bits23(i), column = packed query row
     f32x16 S = f32x16{};
 #pragma unroll
     for (int s = 0; s < DS; ++s)
@@ -251,7 +217,7 @@ void decode_attn_kernel(DecodeArgs a) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int row = 8 * (v >> 2) + 4 * g + (v & 3);
-        if (k0 + swap23(row) >= vis_end) S[v] = -INFINITY;
+        if (k0 + swap_bits23(row) >= vis_end) S[v] = -INFINITY;
       }
     }
     float mx = S[0];

@@ -18,7 +18,7 @@
 // launch: its ranges have workgroups of their own or follow a shard's range.
 //
 // Step.  S^T = K Q^T with K rows and Q rows from LDS, P in the B layout of the
-// PV product because LDS row r of a K step holds key swap23(r); O^T += V^T
+// PV product because LDS row r of a K step holds key swap_bits23(r); O^T += V^T
 // P^T with V read transposed.  Rows sit in LDS with their 16-byte chunks
 // permuted by the row, which keeps the reads free of bank conflicts.
 //
@@ -32,35 +32,13 @@
 #include <cmath>
 #include <type_traits>
 
-#include "common.hpp"
+#include "tiles.hpp"
 
 namespace {
 
 constexpr int PK_WAVES = 4;
 constexpr int PK_KEYS = 32;  // keys per step
 constexpr float PK_SLACK = 8.0f;  // log2 slack before the reference is raised
-constexpr int kPkBufferFlags = 0x00020000;  // raw 32-bit buffer access (word 3 of the resource)
-
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
-__device__ constexpr bf16x2 kOnes2 = {(__bf16)1.0f, (__bf16)1.0f};
-
-// 16 bytes per lane from global memory straight into LDS at lds_base + 16*l.
-__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t rsrc, uint32_t voffset,
-                                      uint32_t lds_base) {
-  asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds"
-               :
-               : "v"(voffset), "s"(rsrc), "{m0}"(lds_base)
-               : "memory");
-}
-
-__device__ __forceinline__ int swap23(int r) {
-  return (r & ~12) | ((r >> 1) & 4) | ((r << 1) & 8);
-}
 
 struct PackedArgs {
   const uint16_t* Q;  // bf16 [Tq, Hq, D]
@@ -137,7 +115,6 @@ void packed_attn_kernel(PackedArgs a) {
   // Chunk c of LDS row r (Q and K) sits at chunk position c ^ swz(r): 16
   // consecutive rows' chunks of one column fall in different banks.
   auto swz = [](int r) { return CPR == 16 ? (r & 15) : ((r >> 1) & 7); };
-  auto vswz = [](int r) { return (4 * ((r * CPR) / 16)) % CPR; };  // V, for transposing reads
   // Keys [begin, end) of one key array, in steps of KS * 32; the last may lie
   // past the end for some key sets (loads re-read the first key; masked).
   struct Span {
@@ -178,9 +155,9 @@ void packed_attn_kernel(PackedArgs a) {
     const uint32_t bytes = gen ? span[1].bytes : span[0].bytes;
     const int begin = gen ? span[1].begin : span[0].begin, end = gen ? span[1].end : span[0].end;
     const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(gen ? span[1].k : span[0].k), (short)0, (int)bytes, kPkBufferFlags);
+        const_cast<uint16_t*>(gen ? span[1].k : span[0].k), (short)0, (int)bytes, kBufferFlags);
     const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t*>(gen ? span[1].v : span[0].v), (short)0, (int)bytes, kPkBufferFlags);
+        const_cast<uint16_t*>(gen ? span[1].v : span[0].v), (short)0, (int)bytes, kBufferFlags);
     const uint32_t st =
         __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)stage_of(j)) + grp * 1024;
     const int k0 = key0(j);
@@ -188,13 +165,13 @@ void packed_attn_kernel(PackedArgs a) {
     for (int i = 0; i < SEGS; ++i) {
       const int slot = (i * NG + grp) * 64 + lane;
       const int r = slot / CPR, c = slot % CPR;
-      int kk = k0 + swap23(r), kv = k0 + r;
+      int kk = k0 + swap_bits23(r), kv = k0 + r;
       kk = kk < end ? kk : begin;
       kv = kv < end ? kv : begin;
-      dma16(kr, (uint32_t)kk * row_bytes + head_off + (uint32_t)(c ^ swz(r)) * 16u,
-            st + i * NG * 1024);
-      dma16(vr, (uint32_t)kv * row_bytes + head_off + (uint32_t)(c ^ vswz(r)) * 16u,
-            st + L::STEP + i * NG * 1024);
+      lds_dma16(kr, (uint32_t)kk * row_bytes + head_off + (uint32_t)(c ^ swz(r)) * 16u,
+                st + i * NG * 1024);
+      lds_dma16(vr, (uint32_t)kv * row_bytes + head_off + (uint32_t)(c ^ v_swizzle<D>(r)) * 16u,
+                st + L::STEP + i * NG * 1024);
     }
   };
 
@@ -222,20 +199,9 @@ void packed_attn_kernel(PackedArgs a) {
   const lds_u8* const q_lds = (lds_u8*)smem + grp * RT * 32 * D * 2;
   auto q_frag = [&](int t, int s) { return frag(q_lds + t * 32 * D * 2, s); };
   uint32_t vtr_base[DT];
-  {
-    const int a16 = lane >> 4, jj = (lane >> 2) & 3, q = lane & 3;
-    const int trow = 8 * (a16 >> 1) + jj;
-    const int cb = 2 * (a16 & 1) + (q >> 1);
-#pragma unroll
-    for (int e = 0; e < DT; ++e)
-      vtr_base[e] = trow * (2 * D) + 16 * ((4 * e + cb) ^ vswz(trow)) + 8 * (q & 1);
-  }
+  v_tr_base<D>(lane, vtr_base);
   auto v_frag = [&](const lds_u8* sV, int c, int e) -> bf16x8 {
-    const lds_u8* b = sV + vtr_base[e] + (16 * c) * (2 * D);
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)b);
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(b + 4 * (2 * D)));
-    return __builtin_bit_cast(bf16x8,
-                              (s16x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+    return v_tr_read<D>(sV + vtr_base[e] + (16 * c) * (2 * D));
   };
 
   f32x16 acc[RT][DT];
@@ -301,7 +267,7 @@ void packed_attn_kernel(PackedArgs a) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int row = 8 * (v >> 2) + 4 * g + (v & 3);
-          if (k0 + swap23(row) >= vis_end) S[v] = -INFINITY;
+          if (k0 + swap_bits23(row) >= vis_end) S[v] = -INFINITY;
         }
       };
       auto row_max = [&](const f32x16& S) {
