@@ -50,7 +50,7 @@ PEAK_HBM_GBPS = 8000.0      # MI355X HBM3E peak (published)
 # the attention kernel's sources: the HBM-traffic figure is used only while
 # they are unchanged since the counters were taken
 ATTN_SRCS = [os.path.join(ROOT, "paper_2607_20457_amd", "csrc", f)
-             for f in ("attn_kernel.hpp", "attn.hip", "attn_d128.hip", "common.hpp")]
+             for f in ("attn_kernel.hpp", "attn.hip", "attn_d128.hip", "tiles.hpp", "common.hpp")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
 

@@ -545,7 +545,9 @@ int launch_packed_d(const PackedArgs& a, int tiles, int64_t nwg, hipStream_t str
 // three tiles per wave 5 tiles take 52.8 / 56 us, 6 tiles at 16 x 8192 keys
 // 160 / 168 us: their accumulators fill the registers.  At d = 64, 5 x 3000
 // keys of 16 heads, 2 tiles: 46.5 / 19.2 us; 16 x 2000, 16 / 8 heads, 4 tiles:
-// 38.4 / 27.9 us.
+// 38.4 / 27.9 us; a query step of 6 tiles, 16 / 4 heads, 8 x 4096 keys 33.5 /
+// 25.4, 16 / 16 heads, 16 x 8192 185 / 181 (partials alone: packed_partial in
+// api.hip).
 int packed_tokens(int Hq, int Hkv, int d) {
   const int group = Hq / Hkv, tiles = d == 64 ? 6 : 4;
   return (d == 64 || d == 128) && group >= 1 && group <= 32 ? tiles * (32 / group) : 0;
