@@ -589,6 +589,11 @@ void attn_fwd_kernel(KernelArgs ka) {
     // Every matrix phase is the full one: M_0 multiplies the zeroed V of
     // stage 2 by P = 0, and M_ntiles computes an S that is never used (from
     // finite LDS data).
+    // The loop and its peeled first phase begin on an instruction cache line, so
+    // that their time does not hang on the length of the code before them: the
+    // same instructions 12 bytes further on took 0.4 % longer for 128K block 15
+    // and 1.3 % for 10005 tokens of 16 heads of 64 (85.4 us; 84.3 aligned).
+    asm volatile(".p2align 7");
     for (int m = 0; m <= ntiles; ++m) {
       m_phase_begin();
       // group 0's M_m forms the positions of tile m + 2 (read by group 1's
