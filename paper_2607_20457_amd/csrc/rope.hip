@@ -41,9 +41,9 @@ constexpr double kInvTwoPi = 0.15915494309189535;
 // 8 pairs), rotation by the angles of position p + p_add (ROTATE) or a plain
 // copy, 16-byte stores to dst.  `w_pair` and `p` may still be loading: the
 // first data is requested before they are used.  U: steps of heads whose loads
-// are in flight together (no more than the row has).  NT: the loads pass the
-// caches by.
-template <int D, bool ROTATE, int U, bool NT>
+// are in flight together (no more than the row has).  NT: the loads (1), or the
+// stores as well (2), pass the caches by.
+template <int D, bool ROTATE, int U, int NT>
 __device__ __forceinline__ void rope_row(const uint16_t* src, uint16_t* dst, int H, int64_t p,
                                          int64_t p_add, double w_pair, int lane) {
   constexpr int G = D / 16;     // lanes per head: pairs 8j .. 8j+7 each
@@ -114,14 +114,21 @@ __device__ __forceinline__ void rope_row(const uint16_t* src, uint16_t* dst, int
       if (hh < H) {
         u32x4 olo = clo[u], ohi = chi[u];
         if constexpr (ROTATE) rotate(clo[u], chi[u], olo, ohi);
-        *reinterpret_cast<u32x4*>(dst + (int64_t)hh * D) = olo;
-        *reinterpret_cast<u32x4*>(dst + (int64_t)hh * D + D / 2) = ohi;
+        u32x4* const q_lo = reinterpret_cast<u32x4*>(dst + (int64_t)hh * D);
+        u32x4* const q_hi = reinterpret_cast<u32x4*>(dst + (int64_t)hh * D + D / 2);
+        if constexpr (NT == 2) {
+          __builtin_nontemporal_store(olo, q_lo);
+          __builtin_nontemporal_store(ohi, q_hi);
+        } else {
+          *q_lo = olo;
+          *q_hi = ohi;
+        }
       }
     }
   }
 }
 
-template <int D, bool HAS_POS, int U, bool NT>
+template <int D, bool HAS_POS, int U, int NT>
 __global__ __launch_bounds__(kRopeThreads) void rope_kernel(uint16_t* __restrict__ X,
                                                             int64_t rows, int64_t n_rows, int H,
                                                             const int32_t* __restrict__ pos,
@@ -173,13 +180,13 @@ __global__ __launch_bounds__(kRopeThreads) void gather_rope_kernel(
   const uint16_t* src = X + b * x_bstride + (int64_t)p * H * D + 8 * j;
   uint16_t* dst = Y + row * (int64_t)H * D + 8 * j;
   const double w = f.w[8 * j + (hl & 7)];
-  rope_row<D, ROT != 0, 4, false>(src, dst, H, ROT == 2 ? (int64_t)r : (int64_t)p, 0, w, lane);
+  rope_row<D, ROT != 0, 4, 0>(src, dst, H, ROT == 2 ? (int64_t)r : (int64_t)p, 0, w, lane);
 }
 
 typedef void (*RopeKernel)(uint16_t*, int64_t, int64_t, int, const int32_t*, int64_t, RopeFreqs);
 // Steps in flight: as many as the row has, up to four (a row of one step loaded
 // its last heads three times more: 8192 rows of 8 heads of 128 7.2 -> 5.9 us).
-template <int D, bool HAS_POS, bool NT>
+template <int D, bool HAS_POS, int NT>
 RopeKernel rope_for_heads(int H) {
   const int steps = (H + 1024 / D - 1) / (1024 / D);  // of 64 / (D / 16) heads
   return steps <= 1   ? rope_kernel<D, HAS_POS, 1, NT>
@@ -187,10 +194,11 @@ RopeKernel rope_for_heads(int H) {
                       : rope_kernel<D, HAS_POS, 4, NT>;
 }
 template <bool HAS_POS>
-RopeKernel rope_for(int H, int d, bool nt) {
-  return d == 64 ? rope_for_heads<64, HAS_POS, false>(H)
-         : nt    ? rope_for_heads<128, HAS_POS, true>(H)
-                 : rope_for_heads<128, HAS_POS, false>(H);
+RopeKernel rope_for(int H, int d, int nt) {
+  return d == 64   ? rope_for_heads<64, HAS_POS, 0>(H)
+         : nt == 2 ? rope_for_heads<128, HAS_POS, 2>(H)
+         : nt == 1 ? rope_for_heads<128, HAS_POS, 1>(H)
+                   : rope_for_heads<128, HAS_POS, 0>(H);
 }
 
 // The table w_i: the caller's (checked finite) or base^(-2i/d).
@@ -250,15 +258,21 @@ int pulsar_rope(void* X, int batch, int64_t n_rows, int H, int d, const int32_t*
   const int64_t blocks = (rows + kRopeThreads / 64 - 1) / (kRopeThreads / 64);  // a wave per row
   if (blocks > 0x7fffffff) return PULSAR_EUNSUPPORTED;
   auto s = (hipStream_t)stream;
-  // Nontemporal loads from 256 MB on, the size of the last-level cache, for heads
-  // of 128.  Q and K together, plain / nontemporal, us, right after the projections
-  // that write them and (repeated) rotated over and over: 32768 tokens, 32 / 8
-  // heads (256 and 64 MB) 107.5 / 107.3, repeated 115.5 / 104.3; 32 / 32 heads (256
-  // MB each) 174 / 167, 188 / 186; 65536 tokens, 32 / 8 heads 221 / 209, 240 / 234.
-  // Smaller ones lose when repeated (128 MB 51.6 / 54.2), and at d 64 every load
-  // is half a cache line, which is then fetched twice (128 MB each 78 / 107).
-  // Nontemporal stores as well take longer after projections (256 and 64 MB 113.7).
-  const bool nt = rows * H * d * 2 >= (int64_t)256 << 20;
+  // Nontemporal loads from 256 MB on, the size of the last-level cache, and stores
+  // too from three times that, of which the cache keeps little for the next
+  // reader; for heads of 128.  Q and K together, us, all cached / loads / loads and
+  // stores nontemporal, right after the projections that write them, and over
+  // several tensors in turn:
+  //   tokens, heads (Q and K, MB)    after projections      in turn
+  //   32768, 32 / 8   (256,  64)   106.5 / 105.5 / 112.4  123.7 / 118.0 / 107.2
+  //   65536, 32 / 8   (512, 128)   223.5 / 210.2 / 218.1  244.1 / 231.8 / 209.0
+  //   98304, 32 / 8   (768, 192)   349.2 / 330.6 / 320.2  366.7 / 352.4 / 329.9
+  //   131072, 32 / 8 (1024, 256)   468.7 / 444.6 / 434.8  490.3 / 469.8 / 449.0
+  // Smaller ones lose when rotated again and again (128 MB 51.6 / 54.2), and at
+  // d 64 every load is half a cache line, which is then fetched twice (128 MB each
+  // 78 / 107).
+  const int64_t bytes = rows * H * d * 2;
+  const int nt = bytes >= (int64_t)768 << 20 ? 2 : bytes >= (int64_t)256 << 20 ? 1 : 0;
   const RopeKernel kern = pos ? rope_for<true>(H, d, nt) : rope_for<false>(H, d, nt);
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kRopeThreads), 0, s, (uint16_t*)X, rows,
                      n_rows, H, pos, pos_offset, f);

@@ -281,3 +281,24 @@ def test_rope_of_256_mb_equals_its_halves(H, posmode):
         else:
             P.rope_(part, pos[:, i * (n // 2):(i + 1) * (n // 2)].contiguous())
     assert torch.equal(X, torch.cat(parts, 1))
+
+
+@pytest.mark.parametrize("H", [8, 9, 33])
+@pytest.mark.parametrize("posmode", ["rows", "array"])
+def test_rope_of_768_mb_equals_its_quarters(H, posmode):
+    # from 768 MB on (d 128) the stores pass the caches by as well; the quarters
+    # are below the line of the loads too
+    n = ((768 << 20) // (H * 256) + 4) // 4 * 4
+    X = torch.randn((1, n, H, 128), generator=torch.Generator("cuda").manual_seed(80 + H),
+                    device="cuda", dtype=torch.bfloat16)
+    pos = None if posmode == "rows" else \
+        torch.randint(0, 140000, (1, n), dtype=torch.int32, device="cuda")
+    parts = [p.clone() for p in X.split(n // 4, 1)]
+    assert X.numel() * 2 >= 768 << 20 and parts[0].numel() * 2 < 256 << 20
+    P.rope_(X, pos)
+    for i, part in enumerate(parts):
+        if pos is None:
+            P.rope_(part, pos_offset=i * (n // 4))
+        else:
+            P.rope_(part, pos[:, i * (n // 4):(i + 1) * (n // 4)].contiguous())
+    assert torch.equal(X, torch.cat(parts, 1))
